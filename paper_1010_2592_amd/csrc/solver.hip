@@ -826,6 +826,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
     const int nbv = nblocks_for(n);
     const long ps = part_stride(c->g);
     const size_t cs = sizeof(C<T>);
+    const long vs = (long)(l + 1) * n;   // rhs stride of R and U
     const int max_outer = P.max_outer;
     const int max_steps = max_outer * l;
     c->bytes_acc = 0;
@@ -1104,7 +1105,6 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
     g_bicg.need_bicg = 1;
     Gate g_run;
     g_run.seed = seed;
-    const long vs = (long)(l + 1) * n;   // rhs stride of R and U
     DslashArgs<T> d1 = ds_args<T>(c, P.neg_mu, true);
     d1.in_rs = vs;
     d1.out_rs = n;
