@@ -111,17 +111,53 @@ __device__ inline void block_reduce_store(double (&v)[NV], double *out, int stri
     }
 }
 
-// Reduce NV doubles over the 64 lanes of a wavefront (fixed shuffle tree, so
-// the same data always gives the same bits) and store them from lane 0 at
-// out[k * stride].
+// x + the value 32 (16) lanes away (H = 32: lane ^ 32, H = 16: lane ^ 16):
+// the swap instruction exchanges the upper half (odd rows) of one register
+// with the lower half (even rows) of the other, so with x in both the sum of
+// the two results is x_i + x_{i ^ H} in every lane.
+template <int H>
+__device__ __forceinline__ double swap_add(double x) {
+    const unsigned lo = (unsigned)__double2loint(x), hi = (unsigned)__double2hiint(x);
+    if constexpr (H == 32) {
+        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    } else {
+        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    }
+}
+// x + x of the lane R away in its row of 16 (DPP row rotate)
+template <int R>
+__device__ __forceinline__ double ror_add(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x120 + R, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x120 + R, 0xF, 0xF, false);
+    return x + __hiloint2double(hi, lo);
+}
+// The sum of x over the 64 lanes, in every lane, in the order of a shuffle-
+// down tree (32, 16, .. 1 lanes apart): after the step of width h, lanes that
+// differ by a multiple of h hold the same sum, so each rotation by h/2 adds
+// the tree's partner.  All VALU: a shuffle goes through LDS, and the 36
+// dependent trips of three shuffled sums cost the 12-source 16^3x32 Mv
+// stencil 15 to 20 us a launch.
+__device__ __forceinline__ double wave_sum(double x) {
+    x = swap_add<32>(x);
+    x = swap_add<16>(x);
+    x = ror_add<8>(x);
+    x = ror_add<4>(x);
+    x = ror_add<2>(x);
+    return ror_add<1>(x);
+}
+
+// Reduce NV doubles over the 64 lanes of a wavefront (the same data always
+// gives the same bits) and store them from lane 0 at out[k * stride].
 template <int NV>
-__device__ inline void wave_reduce_store(double (&v)[NV], double *out, long stride) {
+__device__ inline void wave_reduce_store(const double (&v)[NV], double *out, long stride) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-        double x = v[k];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
+        const double x = wave_sum(v[k]);
         if (lane == 0) out[(size_t)k * stride] = x;
     }
 }

@@ -41,16 +41,13 @@ __global__ __launch_bounds__(BLOCK) void dslash_kernel(DslashArgs<T> a) {
     dslash_body<T, EPI, G5IN>(a, blockIdx.x);
 }
 
-// wavefronts per block of the chunked stencil: 4 (FP64: two blocks per CU by
+// 4 wavefronts per block of the chunked stencil (FP64: two blocks per CU by
 // the 74 KB of staged links and by registers; FP32: three, 96 chunks resident
 // per XCD, whose z-t checkerboard reads overlap in L2 better than those of
-// one 12-wavefront block per CU, 2863 against 2690 GB/s on 16^3x32 with 12
-// right-hand sides)
-template <typename T> constexpr int chunk_waves() { return 4; }
-
+// one 12-wavefront block per CU)
 template <typename T, int EPI, bool G5IN>
-__global__ __launch_bounds__(64 * chunk_waves<T>()) void dslash_chunk_kernel(DslashArgs<T> a) {
-    dslash_chunk<T, EPI, G5IN, chunk_waves<T>()>(a, blockIdx.x);
+__global__ __launch_bounds__(64 * CHUNK_WAVES) void dslash_chunk_kernel(DslashArgs<T> a) {
+    dslash_chunk<T, EPI, G5IN, CHUNK_WAVES>(a, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -192,7 +189,7 @@ bool stencil_timing_taken() {
 template <typename T>
 void launch_dslash(hipStream_t st, DslashArgs<T> a, int nrhs, int epi, bool g5in) {
     if (nrhs >= CHUNK_MIN_RHS) {
-        dim3 grid((unsigned)dslash_chunk_prepare(a, nrhs)), block(64 * chunk_waves<T>());
+        dim3 grid((unsigned)dslash_chunk_prepare(a, nrhs)), block(64 * CHUNK_WAVES);
 #define MSB_DS(E, G5) dispatch<T>(dslash_chunk_kernel<T, E, G5>, grid, block, st, a)
         if (g5in) {
             if (epi == EPI_PLAIN) MSB_DS(EPI_PLAIN, true);

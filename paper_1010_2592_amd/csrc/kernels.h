@@ -40,7 +40,8 @@ struct DslashArgs {
     int nrhs = 0;
     int nch = 0;               // chunked stencil: 64-site chunks (set by the launcher)
     int tsc = 0;               // chunked stencil: chunks per t-slice, 0 if not whole
-    int per_t = 0;             // chunked stencil: blocks per XCD (per rounded up to tsc)
+    int per_t = 0;             // chunked stencil: blocks per XCD and group (per rounded up to tsc)
+    int rpb = 0;               // chunked stencil: right-hand sides per block (set by the launcher)
     CoefRef ycoef;             // EPI_MV_Y: coefficient of the Mv output
     double2 *y = nullptr;      // EPI_MV_Y accumulator (always FP64)
     const C<T> *w = nullptr;   // EPI_SV2: subtracted from the output
@@ -78,7 +79,21 @@ inline long dslash_prepare(DslashArgs<T> &a, int nrhs) {
 // which stages the links of 64 sites in LDS once for all of them.
 constexpr int CHUNK_MIN_RHS = 4;
 constexpr int CHUNK = 64;
-// Launch geometry of the chunked stencil (blocks = 8 per_t).
+constexpr int CHUNK_WAVES = 4;   // wavefronts per block of the chunked stencil
+// Blocks of the chunked stencil the chip holds at a time: two per CU by the
+// 74 KB of links an FP64 block stages and by its registers, 256 CUs.
+constexpr int CHUNK_RESIDENT = 512;
+// Launch geometry of the chunked stencil; returns its number of blocks.
+//
+// One block per chunk sweeps every right-hand side while the chunks fill the
+// chip's resident blocks four times over or more.  Below that the last,
+// partly filled round of blocks costs too much, and each block takes at most
+// one right-hand side per wavefront instead (balanced groups), staging its
+// links again from the caches: 12 sources on 12^3x24 (648 chunks, 1.3
+// rounds) took 94 / 80 us per Mv (with / without r~) in one group and take
+// 88 / 76 in three; on 8^4 (64 chunks) 16 vectors took 19 us, now 11 (plain
+// epilogue).  With 2048 chunks (16^3x32, 12 sources) one group stays ahead,
+// 244 us against 250, and with 6 sources, 118 against 124.
 template <typename T>
 inline long dslash_chunk_prepare(DslashArgs<T> &a, int nrhs) {
     a.nrhs = nrhs;
@@ -88,7 +103,11 @@ inline long dslash_chunk_prepare(DslashArgs<T> &a, int nrhs) {
     a.tsc = (sites_t % CHUNK == 0) ? sites_t / CHUNK : 0;
     a.per_t = a.tsc ? ((a.per + a.tsc - 1) / a.tsc) * a.tsc : a.per;
     a.sstride = 1 << 30;
-    return 8L * a.per_t;
+    int groups = 1;
+    if (a.nch < 4 * CHUNK_RESIDENT) groups = (nrhs + CHUNK_WAVES - 1) / CHUNK_WAVES;
+    a.rpb = (nrhs + groups - 1) / groups;
+    groups = (nrhs + a.rpb - 1) / a.rpb;
+    return 8L * a.per_t * groups;
 }
 
 // link force: pairs (c, p, q), the gradient of sum c Re <p, D(mu) q>

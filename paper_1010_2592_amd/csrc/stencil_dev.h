@@ -583,20 +583,19 @@ __device__ __forceinline__ void dslash_body(const DslashArgs<T> &a, int p) {
     dslash_site_block<T, EPI, G5IN>(a, sblk, L - sblk * a.nrhs);
 }
 
-// Chunked stencil for batches: one block of NW wavefronts per 64-site chunk.
-// The block first stages the chunk's eight links per site (forward U_nu(x)
-// and backward U_nu(x - nu)) in LDS, then its wavefronts take the right-hand
-// sides in turn, one site per lane, reading the links from LDS: the links
-// cross the memory fabric once per chunk instead of once per right-hand side
-// (which is what bounded the site-block stencil on batches).  Chunks are
-// dealt XCD-aware: XCD p % 8 owns a contiguous slab of chunks, walked with
-// the time coordinate varying fastest so that the t -/+ 1 neighbour planes
-// were read moments earlier by the same XCD.  Arithmetic, per site and per
-// partial, is the site-block stencil's, bit for bit.
-template <typename T, int EPI, bool G5IN, int NW>
-__device__ __forceinline__ void dslash_chunk(const DslashArgs<T> &a, int p) {
-    __shared__ C<T> Ls[8 * 9 * CHUNK];
-    const int x8 = p & 7, i = p >> 3;
+// Site offset of the backward neighbour in direction nu.
+__device__ __forceinline__ int back_neighbour(const Geom &g, int nu, int s) {
+    const int d = nu == 0 ? 1 : nu == 1 ? g.Lx : nu == 2 ? g.Lx * g.Ly : g.Lx * g.Ly * g.Lz;
+    const int L = nu == 0 ? g.Lx : nu == 1 ? g.Ly : nu == 2 ? g.Lz : g.Lt;
+    return (s / d) % L == 0 ? s + (L - 1) * d : s - d;
+}
+
+// Chunk of a block of the chunked and the split stencil: XCD x8 owns a
+// contiguous slab of chunks, walked with the time coordinate varying fastest
+// (slot i of the slab) so that the t -/+ 1 neighbour planes were read moments
+// earlier by the same XCD.  -1: no chunk.
+template <typename T>
+__device__ __forceinline__ int slab_chunk(const DslashArgs<T> &a, int x8, int i) {
     const int s0 = x8 * a.per;
     int n = a.nch - s0;
     if (n > a.per) n = a.per;
@@ -606,33 +605,51 @@ __device__ __forceinline__ void dslash_chunk(const DslashArgs<T> &a, int p) {
         const int zc = i / ntl;
         c = (i - zc * ntl) * a.tsc + zc;
     }
-    if (c >= n) return;
-    const int chunk = s0 + c;
-    const int V = a.g.V, Lx = a.g.Lx, Ly = a.g.Ly, Lz = a.g.Lz, Lt = a.g.Lt;
+    return c < n ? s0 + c : -1;
+}
+
+// Chunked stencil for batches: one block of NW wavefronts per 64-site chunk
+// and group of a.rpb right-hand sides (dslash_chunk_prepare says why).  The
+// block first stages the chunk's eight links per site (forward U_nu(x) and
+// backward U_nu(x - nu)) in LDS, then its wavefronts take the group's
+// right-hand sides in turn, one site per lane, reading the links from LDS:
+// the links cross the memory fabric once per chunk instead of once per
+// right-hand side.  Each wavefront stages whole directions, one site per
+// lane, with all 18 loads of a direction in flight and the neighbour worked
+// out once; a loop over flat element indices (with two divisions and one
+// exposed trip to memory per element) took 20 us of a 12-source 16^3x32
+// launch (plain epilogue 226 us, now 206; 4 sources 80 us, now 64).  Which
+// group a block takes varies slowest, so a launch sweeps the lattice group
+// after group (one group's input and output stay nearer the caches; with the
+// groups of a chunk side by side 12 sources in threes took 240 us, not 214).
+template <typename T, int EPI, bool G5IN, int NW>
+__device__ __forceinline__ void dslash_chunk(const DslashArgs<T> &a, int p) {
+    __shared__ C<T> Ls[8 * 9 * CHUNK];
+    const int i = p >> 3;
+    const int grp = i / a.per_t;
+    const int chunk = slab_chunk(a, p & 7, i - grp * a.per_t);
+    if (chunk < 0) return;
+    const int V = a.g.V;
     const int base = chunk * CHUNK;
-    for (int idx = threadIdx.x; idx < 8 * 9 * CHUNK; idx += 64 * NW) {
-        const int hp = idx / (9 * CHUNK), e = (idx / CHUNK) % 9;
-        const int s = base + idx % CHUNK;
-        C<T> u = mk<T>(0, 0);
-        if (s < V) {
-            const int nu = hp >> 1;
-            int sl = s;
-            if (hp & 1) {
-                const int x = s % Lx, q1 = s / Lx, yy = q1 % Ly, q2 = q1 / Ly, z = q2 % Lz, t = q2 / Lz;
-                if (nu == 0) sl = (x == 0) ? s + (Lx - 1) : s - 1;
-                else if (nu == 1) sl = (yy == 0) ? s + (Ly - 1) * Lx : s - Lx;
-                else if (nu == 2) sl = (z == 0) ? s + (Lz - 1) * Lx * Ly : s - Lx * Ly;
-                else sl = (t == 0) ? s + (Lt - 1) * Lx * Ly * Lz : s - Lx * Ly * Lz;
-            }
-            u = a.U[((size_t)nu * 9 + e) * V + sl];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
+    const int sl = base + lane < V ? base + lane : V - 1;   // lanes past the lattice stage its last site
+    for (int nu = w; nu < 4; nu += NW) {
+        const C<T> *U = a.U + (size_t)nu * 9 * (unsigned)V;
+        const int sb = back_neighbour(a.g, nu, sl);
+        C<T> u[18];
+#pragma unroll
+        for (int e = 0; e < 9; ++e) {
+            u[e] = elem(U, e, V, sl);
+            u[9 + e] = elem(U, e, V, sb);
         }
-        Ls[idx] = u;
+#pragma unroll
+        for (int e = 0; e < 18; ++e) Ls[(nu * 18 + e) * CHUNK + lane] = u[e];
     }
     __syncthreads();
     const LdsLinks<T> lk{Ls, base};
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
-    for (int rhs = w; rhs < a.nrhs; rhs += NW) {
+    const int r0 = grp * a.rpb, r1 = r0 + a.rpb < a.nrhs ? r0 + a.rpb : a.nrhs;
+    for (int rhs = r0 + w; rhs < r1; rhs += NW) {
         if (!gate_open(a.gate, rhs)) continue;
         const RhsOps<T> o = rhs_ops<T, EPI>(a, rhs);
         double part[3] = {0.0, 0.0, 0.0};
