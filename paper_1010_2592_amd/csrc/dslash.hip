@@ -4,12 +4,14 @@
 //     - 1/2 sum_nu b_nu(x)   (1 - gamma_nu) e^{+mu d_nu4} U_nu(x)     psi(x+nu)
 //     - 1/2 sum_nu b_nu(x-nu)(1 + gamma_nu) e^{-mu d_nu4} U_nu(x-nu)^+ psi(x-nu)
 //
-// The operator the paper names in Section 1; chiral gamma matrices.  One
-// work-item per lattice site and right-hand side.  Each hop loads the neighbour's 12 complex components (coalesced SoA
-// planes), projects them to a two-component half spinor with (1 -/+ gamma),
-// multiplies the half spinor by the 3x3 link, and reconstructs the lower spin
-// components from the upper ones.  The kernel is HBM-bound (about 1.4 flop
-// per byte in FP64), so it never touches the matrix cores.
+// The operator the paper names in Section 1; chiral gamma matrices.  Each hop
+// loads the neighbour's 12 complex components (coalesced SoA planes), projects
+// them to a two-component half spinor with (1 -/+ gamma), multiplies the half
+// spinor by the 3x3 link, and reconstructs the lower spin components from the
+// upper ones.  About 1.4 flop per byte in FP64, far below what would need the
+// matrix cores.  Two forms of the same sum (bitwise): the chunked one for
+// batches, one lane per site with the links in LDS, and the split one for
+// launches that cannot fill the chip with that, four wavefronts per 64 sites.
 //
 // Epilogues (fused so that the output is written once and never re-read):
 //   EPI_PLAIN  out = scale * [gamma5] D in
@@ -37,8 +39,8 @@ namespace {
 using namespace dev;
 
 template <typename T, int EPI, bool G5IN>
-__global__ __launch_bounds__(BLOCK) void dslash_kernel(DslashArgs<T> a) {
-    dslash_body<T, EPI, G5IN>(a, blockIdx.x);
+__global__ __launch_bounds__(256) void dslash_split_kernel(DslashArgs<T> a) {
+    dslash_split<T, EPI, G5IN>(a, blockIdx.x);
 }
 
 // 4 wavefronts per block of the chunked stencil (FP64: two blocks per CU by
@@ -186,47 +188,26 @@ bool stencil_timing_taken() {
     return k;
 }
 
+template <typename T, int EPI, bool G5IN>
+static void launch_form(hipStream_t st, DslashArgs<T> a, int nrhs) {
+    const int nch = (a.g.V + CHUNK - 1) / CHUNK;
+    if (dslash_use_split(nch, nrhs))
+        dispatch<T>(dslash_split_kernel<T, EPI, G5IN>, dim3((unsigned)dslash_split_prepare(a, nrhs)), dim3(256), st, a);
+    else
+        dispatch<T>(dslash_chunk_kernel<T, EPI, G5IN>, dim3((unsigned)dslash_chunk_prepare(a, nrhs)),
+                    dim3(64 * CHUNK_WAVES), st, a);
+}
+
 template <typename T>
 void launch_dslash(hipStream_t st, DslashArgs<T> a, int nrhs, int epi, bool g5in) {
-    if (nrhs >= CHUNK_MIN_RHS) {
-        dim3 grid((unsigned)dslash_chunk_prepare(a, nrhs)), block(64 * CHUNK_WAVES);
-#define MSB_DS(E, G5) dispatch<T>(dslash_chunk_kernel<T, E, G5>, grid, block, st, a)
-        if (g5in) {
-            if (epi == EPI_PLAIN) MSB_DS(EPI_PLAIN, true);
-            else if (epi == EPI_MV) MSB_DS(EPI_MV, true);
-            else if (epi == EPI_SV) MSB_DS(EPI_SV, true);
-            else if (epi == EPI_SV2) MSB_DS(EPI_SV2, true);
-            else if (epi == EPI_MVN) MSB_DS(EPI_MVN, true);
-            else MSB_DS(EPI_MV_Y, true);
-        } else {
-            if (epi == EPI_PLAIN) MSB_DS(EPI_PLAIN, false);
-            else if (epi == EPI_MV) MSB_DS(EPI_MV, false);
-            else if (epi == EPI_SV) MSB_DS(EPI_SV, false);
-            else if (epi == EPI_SV2) MSB_DS(EPI_SV2, false);
-            else if (epi == EPI_MVN) MSB_DS(EPI_MVN, false);
-            else MSB_DS(EPI_MV_Y, false);
-        }
-#undef MSB_DS
-        return;
-    }
-    dim3 grid((unsigned)dslash_prepare(a, nrhs)), block(BLOCK);
-#define MSB_DS(E, G5) dispatch<T>(dslash_kernel<T, E, G5>, grid, block, st, a)
-    if (g5in) {
-        if (epi == EPI_PLAIN) MSB_DS(EPI_PLAIN, true);
-        else if (epi == EPI_MV) MSB_DS(EPI_MV, true);
-        else if (epi == EPI_SV) MSB_DS(EPI_SV, true);
-        else if (epi == EPI_SV2) MSB_DS(EPI_SV2, true);
-        else if (epi == EPI_MVN) MSB_DS(EPI_MVN, true);
-        else MSB_DS(EPI_MV_Y, true);
-    } else {
-        if (epi == EPI_PLAIN) MSB_DS(EPI_PLAIN, false);
-        else if (epi == EPI_MV) MSB_DS(EPI_MV, false);
-        else if (epi == EPI_SV) MSB_DS(EPI_SV, false);
-        else if (epi == EPI_SV2) MSB_DS(EPI_SV2, false);
-        else if (epi == EPI_MVN) MSB_DS(EPI_MVN, false);
-        else MSB_DS(EPI_MV_Y, false);
-    }
-#undef MSB_DS
+    // gamma5 on the input comes with the plain epilogue alone (D^+)
+    if (g5in) launch_form<T, EPI_PLAIN, true>(st, a, nrhs);
+    else if (epi == EPI_PLAIN) launch_form<T, EPI_PLAIN, false>(st, a, nrhs);
+    else if (epi == EPI_MV) launch_form<T, EPI_MV, false>(st, a, nrhs);
+    else if (epi == EPI_SV) launch_form<T, EPI_SV, false>(st, a, nrhs);
+    else if (epi == EPI_SV2) launch_form<T, EPI_SV2, false>(st, a, nrhs);
+    else if (epi == EPI_MVN) launch_form<T, EPI_MVN, false>(st, a, nrhs);
+    else launch_form<T, EPI_MV_Y, false>(st, a, nrhs);
 }
 
 template void launch_dslash<double>(hipStream_t, DslashArgs<double>, int, int, bool);

@@ -51,8 +51,8 @@ struct DslashArgs {
     long in_rs = 0, out_rs = 0, v_rs = 0, rt_rs = 0, y_rs = 0;
 };
 
-// One block per (256-site block, right-hand side); the launcher sets nsb, per
-// and nrhs.
+// The stencil on nrhs right-hand sides: picks the form (dslash_use_split) and
+// sets its launch geometry.
 template <typename T>
 void launch_dslash(hipStream_t st, DslashArgs<T> a, int nrhs, int epi, bool g5in);
 // Timing of the next launch_dslash on this host thread: its kernel is
@@ -62,8 +62,8 @@ void launch_dslash(hipStream_t st, DslashArgs<T> a, int nrhs, int epi, bool g5in
 void stencil_timing_arm(hipEvent_t start, hipEvent_t stop);
 bool stencil_timing_taken();
 
-// Launch geometry of the site-block stencil: sets nsb, nrhs, per and sstride
-// and returns the number of (virtual) blocks, 8 per, so that block p runs on
+// Geometry of the persistent kernel's stencil (256-site blocks): sets nsb,
+// nrhs, per and sstride and returns the number of (virtual) blocks, 8 per, so that block p runs on
 // XCD p % 8.
 template <typename T>
 inline long dslash_prepare(DslashArgs<T> &a, int nrhs) {
@@ -75,14 +75,38 @@ inline long dslash_prepare(DslashArgs<T> &a, int nrhs) {
     return 8L * a.per;
 }
 
-// Batches of at least this many right-hand sides use the chunked stencil,
-// which stages the links of 64 sites in LDS once for all of them.
-constexpr int CHUNK_MIN_RHS = 4;
 constexpr int CHUNK = 64;
 constexpr int CHUNK_WAVES = 4;   // wavefronts per block of the chunked stencil
 // Blocks of the chunked stencil the chip holds at a time: two per CU by the
 // 74 KB of links an FP64 block stages and by its registers, 256 CUs.
 constexpr int CHUNK_RESIDENT = 512;
+// Slabs of chunks per XCD (see slab_chunk).
+template <typename T>
+inline void dslash_slab_prepare(DslashArgs<T> &a, int nrhs) {
+    a.nrhs = nrhs;
+    a.nch = (a.g.V + CHUNK - 1) / CHUNK;
+    a.per = (a.nch + 7) / 8;
+    const int sites_t = a.g.Lx * a.g.Ly * a.g.Lz;
+    a.tsc = (sites_t % CHUNK == 0) ? sites_t / CHUNK : 0;
+    a.per_t = a.tsc ? ((a.per + a.tsc - 1) / a.tsc) * a.tsc : a.per;
+}
+// Which form: the split stencil (a block per chunk and right-hand side) for
+// one right-hand side, which has no links to share, and while the chip would
+// hold its blocks in two rounds: 8 vectors on 8^4 (512 blocks) take 7.3 us
+// against 9.5 in the chunked form, 6 on 10x9x7x14 (828) 11.6 against 12.4, 16
+// on 8^4 (1024) 12.9 against 10.7 (plain epilogue, FP64).  With 2 or 3
+// right-hand sides the chunked form leaves wavefronts idle and the line lies
+// at three rounds: 2 on 12^3x24 (1296) 22.0 against 24.3 us, 3 (1944) 21.9
+// against 20.9, 2 on 16^3x32 (4096) 49 against 42.
+inline bool dslash_use_split(long nch, int nrhs) {
+    return nrhs == 1 || nch * nrhs < (nrhs < CHUNK_WAVES ? 3 : 2) * (long)CHUNK_RESIDENT;
+}
+// Launch geometry of the split stencil; returns its number of blocks.
+template <typename T>
+inline long dslash_split_prepare(DslashArgs<T> &a, int nrhs) {
+    dslash_slab_prepare(a, nrhs);
+    return 8L * a.per_t * nrhs;
+}
 // Launch geometry of the chunked stencil; returns its number of blocks.
 //
 // One block per chunk sweeps every right-hand side while the chunks fill the
@@ -96,12 +120,7 @@ constexpr int CHUNK_RESIDENT = 512;
 // 244 us against 250, and with 6 sources, 118 against 124.
 template <typename T>
 inline long dslash_chunk_prepare(DslashArgs<T> &a, int nrhs) {
-    a.nrhs = nrhs;
-    a.nch = (a.g.V + CHUNK - 1) / CHUNK;
-    a.per = (a.nch + 7) / 8;
-    const int sites_t = a.g.Lx * a.g.Ly * a.g.Lz;
-    a.tsc = (sites_t % CHUNK == 0) ? sites_t / CHUNK : 0;
-    a.per_t = a.tsc ? ((a.per + a.tsc - 1) / a.tsc) * a.tsc : a.per;
+    dslash_slab_prepare(a, nrhs);
     a.sstride = 1 << 30;
     int groups = 1;
     if (a.nch < 4 * CHUNK_RESIDENT) groups = (nrhs + CHUNK_WAVES - 1) / CHUNK_WAVES;

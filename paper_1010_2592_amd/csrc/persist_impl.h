@@ -149,10 +149,10 @@ __device__ __noinline__ void call_sc_alpha(const ScalarArgs *a, int rhs) { sc_al
 __device__ __noinline__ void call_sc_mr(const ScalarArgs *a, int rhs) { sc_mr_body(*a, rhs); }
 __device__ __noinline__ void call_sc_rel(const ScalarArgs *a, int rhs) { sc_rel_body(*a, rhs); }
 __device__ __noinline__ void call_sc_conv(const ScalarArgs *a, int rhs) { sc_conv_body(*a, rhs); }
-// The site-block stencil in the form that keeps this kernel within the
-// stencil's own register budget (three wavefronts per SIMD): the same
-// arithmetic and per-wavefront partials as dslash_site_block and the chunked
-// stencil, with the one-trip site loop written out in the block function.
+// The stencil of this kernel, one lane per site with the links read from
+// global memory, one hop at a time (two gather buffers would cost the kernel
+// an occupancy step): the same arithmetic and per-wavefront partials as the
+// chunked and the split stencil.
 template <typename T, int EPI, bool G5IN>
 __device__ __forceinline__ void dslash_persist_body(const DslashArgs<T> &a, int p) {
     const int L = (p & 7) * a.per + (p >> 3);
@@ -188,9 +188,9 @@ __device__ __forceinline__ void dslash_persist_body(const DslashArgs<T> &a, int 
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int c = 0; c < 3; ++c) acc[i][c] = mk<T>(0, 0);
-        // the hop order of wilson_site_global (by the parity of z + t),
-        // written out here: through that function the kernel's allocation
-        // needs more than 256 VGPRs and spills
+        // the hops in the order of the parity of z + t (order_parity), written
+        // out here: through a shared function the kernel's allocation needs
+        // more than 256 VGPRs and spills
         const T ff = (t == Lt - 1) ? a.ef * a.bc : a.ef;
         const T fb = (t == 0) ? a.eb * a.bc : a.eb;
         if (order_parity(a.g, s)) {
@@ -262,14 +262,13 @@ __device__ __forceinline__ void dslash_persist_body(const DslashArgs<T> &a, int 
                 out[k * V + s] = o;
                 if (EPI == EPI_MV) {
                     const C<T> r = rt[k * V + s];
-                    part[0] += (double)r.x * o.x + (double)r.y * o.y;
-                    part[1] += (double)r.x * o.y - (double)r.y * o.x;
-                    part[2] += (double)o.x * o.x + (double)o.y * o.y;
+                    part[0] += dot_re(r, o);
+                    part[1] += dot_im(r, o);
+                    part[2] += norm2(o);
                 }
                 if (EPI == EPI_MV_Y) {
                     double2 yv = y[k * V + s];
-                    yv.x += (double)yc.x * o.x - (double)yc.y * o.y;
-                    yv.y += (double)yc.x * o.y + (double)yc.y * o.x;
+                    yv = cadd(yv, ymul(yc, o));
                     y[k * V + s] = yv;
                 }
             }

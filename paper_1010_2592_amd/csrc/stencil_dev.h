@@ -1,8 +1,10 @@
 // Device body of the Wilson-Dirac stencil D_w(mu) (see dslash.hip for the
-// operator and the epilogues).  Shared by the one-launch-per-stage kernels and
-// by the persistent kernel, which calls dslash_body for each of its virtual
-// blocks.
+// operator and the epilogues): the chunked form for batches, the split form
+// for small launches, and the pieces that the persistent kernel's own form
+// shares with them.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -16,6 +18,27 @@ __device__ __forceinline__ Z mulcode(Z z) {
     else if constexpr (CODE == 1) return cneg(z);
     else if constexpr (CODE == 2) return ctimes_i(z);
     else return ctimes_mi(z);
+}
+
+// The terms of the epilogues' sums, Re and Im conj(a) b, |a|^2 and c a, with
+// the multiply-add of each written out: left to the compiler, which product
+// of such a sum is rounded differs between the stencil's forms.
+template <typename Z>
+__device__ __forceinline__ double dot_re(Z a, Z b) {
+    return __builtin_fma((double)a.x, (double)b.x, (double)a.y * b.y);
+}
+template <typename Z>
+__device__ __forceinline__ double dot_im(Z a, Z b) {
+    return __builtin_fma((double)a.x, (double)b.y, -((double)a.y * b.x));
+}
+template <typename Z>
+__device__ __forceinline__ double norm2(Z a) {
+    return __builtin_fma((double)a.x, (double)a.x, (double)a.y * a.y);
+}
+template <typename Z>
+__device__ __forceinline__ double2 ymul(Z c, Z a) {
+    return d2(__builtin_fma((double)c.x, (double)a.x, -((double)c.y * a.y)),
+              __builtin_fma((double)c.y, (double)a.x, (double)c.x * a.y));
 }
 
 constexpr int ONE = 0, NEG = 1, I = 2, MI = 3;
@@ -119,27 +142,15 @@ template <typename E>
 __device__ __forceinline__ E &elem(E *__restrict__ p, int k, int V, int s) {
     return (p + (size_t)k * (unsigned)V)[(unsigned)s];
 }
-// UB = false: the plain signed index k V + s (the site-block kernel's form,
-// which the compiler schedules in fewer registers there)
-template <bool UB, typename E>
-__device__ __forceinline__ E &elem_at(E *__restrict__ p, int k, int V, int s) {
-    if constexpr (UB) return elem(p, k, V, s);
-    else return p[k * V + s];
-}
-
-// An operand read once per sweep (v, w, r~, y): with UB (the chunked form) streamed
-// past L2, like the output, so that it does not evict neighbour spinors.
-template <bool UB, typename E>
+// An operand the chunked form reads once per sweep (v, w, r~, y): streamed
+// past L2, like its output, so that it does not evict neighbour spinors.
+template <typename E>
 __device__ __forceinline__ E ld_stream(const E *__restrict__ p, int k, int V, int s) {
-    if constexpr (UB) {
-        const E &q = elem(p, k, V, s);
-        E r;
-        r.x = __builtin_nontemporal_load(&q.x);
-        r.y = __builtin_nontemporal_load(&q.y);
-        return r;
-    } else {
-        return p[k * V + s];
-    }
+    const E &q = elem(p, k, V, s);
+    E r;
+    r.x = __builtin_nontemporal_load(&q.x);
+    r.y = __builtin_nontemporal_load(&q.y);
+    return r;
 }
 
 // The 12 components of psi(s) ([gamma5] applied: lower spins negated).
@@ -164,28 +175,14 @@ __device__ __forceinline__ void project(const C<T> (&b)[12], C<T> (&h)[2][3]) {
     }
 }
 
-// Where a hop finds its link: in global memory ([4][3][3][V], entry stride V)
-// or staged in LDS for a 64-site chunk ([8 hops][9][CHUNK], stride CHUNK).
-template <typename T>
-struct GlobalLinks {
-    static constexpr bool staged = false;
-    const C<T> *U;
-    int V;
-    __device__ __forceinline__ const C<T> *at(int nu, int bwd, int sl, int) const {
-        (void)bwd;
-        return U + (size_t)nu * 9 * V + sl;
-    }
-    __device__ __forceinline__ int stride() const { return V; }
-};
+// The links staged in LDS for a 64-site chunk: [8 hops][9][CHUNK].
 template <typename T>
 struct LdsLinks {
-    static constexpr bool staged = true;
     const C<T> *L;
     int base;   // first site of the chunk
-    __device__ __forceinline__ const C<T> *at(int nu, int bwd, int, int s) const {
+    __device__ __forceinline__ const C<T> *at(int nu, int bwd, int s) const {
         return L + (2 * nu + bwd) * 9 * CHUNK + (s - base);
     }
-    __device__ __forceinline__ int stride() const { return CHUNK; }
 };
 
 // Lx = 16 in the chunked form: the 16 lanes of each row of a wavefront hold
@@ -280,64 +277,6 @@ __device__ __forceinline__ void odd_finish(C<T> (&acc)[4][3], const C<T> (&b)[12
     }
 }
 
-// The Wilson operator at site s with the links read from global memory
-// ([4][3][3][V]; the site-block and persistent forms): one hop at a time,
-// since two gather buffers would cost the site-block kernel an occupancy
-// step.  Leaves scale [gamma5] D [gamma5] psi(s) in acc.
-template <typename T, bool G5IN>
-__device__ __forceinline__ void wilson_site_global(const DslashArgs<T> &a, const C<T> *__restrict__ U,
-                                                   const C<T> *__restrict__ in, int s, C<T> (&acc)[4][3]) {
-    const int V = a.g.V, Lx = a.g.Lx, Ly = a.g.Ly, Lz = a.g.Lz, Lt = a.g.Lt;
-    const int sxy = Lx * Ly, sxyz = Lx * Ly * Lz;
-    const int x = s % Lx;
-    const int r1 = s / Lx;
-    const int yy = r1 % Ly;
-    const int r2 = r1 / Ly;
-    const int z = r2 % Lz;
-    const int t = r2 / Lz;
-    const T ff = (t == Lt - 1) ? a.ef * a.bc : a.ef;
-    const T fb = (t == 0) ? a.eb * a.bc : a.eb;
-    auto hx = [&]() __attribute__((always_inline)) {
-        const int sf = (x == Lx - 1) ? s - (Lx - 1) : s + 1;
-        const int sb = (x == 0) ? s + (Lx - 1) : s - 1;
-        hop<T, 0, -1, false, G5IN>(acc, in, U + s, V, V, sf, (T)1);
-        hop<T, 0, +1, true, G5IN>(acc, in, U + sb, V, V, sb, (T)1);
-    };
-    auto hy = [&]() __attribute__((always_inline)) {
-        const int sf = (yy == Ly - 1) ? s - (Ly - 1) * Lx : s + Lx;
-        const int sb = (yy == 0) ? s + (Ly - 1) * Lx : s - Lx;
-        hop<T, 1, -1, false, G5IN>(acc, in, U + (size_t)9 * V + s, V, V, sf, (T)1);
-        hop<T, 1, +1, true, G5IN>(acc, in, U + (size_t)9 * V + sb, V, V, sb, (T)1);
-    };
-    auto hz = [&]() __attribute__((always_inline)) {
-        const int sf = (z == Lz - 1) ? s - (Lz - 1) * sxy : s + sxy;
-        const int sb = (z == 0) ? s + (Lz - 1) * sxy : s - sxy;
-        hop<T, 2, -1, false, G5IN>(acc, in, U + (size_t)18 * V + s, V, V, sf, (T)1);
-        hop<T, 2, +1, true, G5IN>(acc, in, U + (size_t)18 * V + sb, V, V, sb, (T)1);
-    };
-    auto ht = [&]() __attribute__((always_inline)) {
-        const int sf = (t == Lt - 1) ? s - (Lt - 1) * sxyz : s + sxyz;
-        const int sb = (t == 0) ? s + (Lt - 1) * sxyz : s - sxyz;
-        hop<T, 3, -1, false, G5IN>(acc, in, U + (size_t)27 * V + s, V, V, sf, ff);
-        hop<T, 3, +1, true, G5IN>(acc, in, U + (size_t)27 * V + sb, V, V, sb, fb);
-    };
-    C<T> b[12];
-    if (order_parity(a.g, s)) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) acc[i][c] = mk<T>(0, 0);
-        hz(); ht(); hx(); hy();
-        load_site<T, G5IN>(in, V, s, b);
-        odd_finish<T>(acc, b, a.diag, a.scale, a.g5out);
-    } else {
-        load_site<T, G5IN>(in, V, s, b);
-        diag_start<T>(acc, b, (T)-2 * a.diag);
-        hx(); hy(); hz(); ht();
-        even_finish<T>(acc, a.scale, a.g5out);
-    }
-}
-
 // The stencil and its epilogue for sites s0, s0 + sstride, ... < V of one
 // right-hand side.  sstride exceeds V, so the loop body runs at most once;
 // keeping it a loop with a run-time bound (and every address derived from s)
@@ -345,8 +284,8 @@ __device__ __forceinline__ void wilson_site_global(const DslashArgs<T> &a, const
 // right-hand sides.  With links in LDS the neighbours are gathered two hops
 // ahead: while hop k is multiplied, the spinors of hops k + 1 and k + 2 are
 // in flight (two 12-component buffers), in the parity order above.
-template <typename T, int EPI, bool G5IN, typename LK>
-__device__ __forceinline__ void dslash_sites(const DslashArgs<T> &a, const LK &lk, const C<T> *__restrict__ in,
+template <typename T, int EPI, bool G5IN>
+__device__ __forceinline__ void dslash_sites(const DslashArgs<T> &a, const LdsLinks<T> &lk, const C<T> *__restrict__ in,
                                              C<T> *__restrict__ out, const C<T> *__restrict__ v,
                                              const C<T> *__restrict__ rt, double2 *__restrict__ y, C<T> yc,
                                              T sig0, const C<T> *__restrict__ wsub,
@@ -354,9 +293,6 @@ __device__ __forceinline__ void dslash_sites(const DslashArgs<T> &a, const LK &l
     const int V = a.g.V;
     for (int s = s0; s < V; s += a.sstride) {
     C<T> acc[4][3];
-    if constexpr (!LK::staged) {
-        wilson_site_global<T, G5IN>(a, lk.U, in, s, acc);
-    } else {
     const int Lx = a.g.Lx, Ly = a.g.Ly, Lz = a.g.Lz, Lt = a.g.Lt;
     const int sxy = Lx * Ly, sxyz = Lx * Ly * Lz;
     const int x = s % Lx;
@@ -365,7 +301,7 @@ __device__ __forceinline__ void dslash_sites(const DslashArgs<T> &a, const LK &l
     const int r2 = r1 / Ly;
     const int z = r2 % Lz;
     const int t = r2 / Lz;
-    const int us = lk.stride();
+    constexpr int us = CHUNK;
     const T ff = (t == Lt - 1) ? a.ef * a.bc : a.ef;
     const T fb = (t == 0) ? a.eb * a.bc : a.eb;
     const int xf = (x == Lx - 1) ? s - (Lx - 1) : s + 1;
@@ -388,27 +324,27 @@ __device__ __forceinline__ void dslash_sites(const DslashArgs<T> &a, const LK &l
         load_site<T, G5IN>(in, V, zb, bB);
         project<T, 2, -1>(bA, h);
         load_site<T, G5IN>(in, V, tf, bA);
-        hop_h<T, 2, -1, false>(acc, h, lk.at(2, 0, s, s), us, (T)1);
+        hop_h<T, 2, -1, false>(acc, h, lk.at(2, 0, s), us, (T)1);
         project<T, 2, +1>(bB, h);
         load_site<T, G5IN>(in, V, tb, bB);
-        hop_h<T, 2, +1, true>(acc, h, lk.at(2, 1, zb, s), us, (T)1);
+        hop_h<T, 2, +1, true>(acc, h, lk.at(2, 1, s), us, (T)1);
         project<T, 3, -1>(bA, h);
         load_site<T, G5IN>(in, V, s, bA);    // the centre
-        hop_h<T, 3, -1, false>(acc, h, lk.at(3, 0, s, s), us, ff);
+        hop_h<T, 3, -1, false>(acc, h, lk.at(3, 0, s), us, ff);
         project<T, 3, +1>(bB, h);
         load_site<T, G5IN>(in, V, yf, bB);
-        hop_h<T, 3, +1, true>(acc, h, lk.at(3, 1, tb, s), us, fb);
+        hop_h<T, 3, +1, true>(acc, h, lk.at(3, 1, s), us, fb);
         project<T, 0, -1>(bA, h);
         x_rotate<T, true>(h);
-        hop_h<T, 0, -1, false>(acc, h, lk.at(0, 0, s, s), us, (T)1);
+        hop_h<T, 0, -1, false>(acc, h, lk.at(0, 0, s), us, (T)1);
         project<T, 0, +1>(bA, h);
         x_rotate<T, false>(h);
-        hop_h<T, 0, +1, true>(acc, h, lk.at(0, 1, xb, s), us, (T)1);
+        hop_h<T, 0, +1, true>(acc, h, lk.at(0, 1, s), us, (T)1);
         project<T, 1, -1>(bB, h);
         load_site<T, G5IN>(in, V, yb, bB);
-        hop_h<T, 1, -1, false>(acc, h, lk.at(1, 0, s, s), us, (T)1);
+        hop_h<T, 1, -1, false>(acc, h, lk.at(1, 0, s), us, (T)1);
         project<T, 1, +1>(bB, h);
-        hop_h<T, 1, +1, true>(acc, h, lk.at(1, 1, yb, s), us, (T)1);
+        hop_h<T, 1, +1, true>(acc, h, lk.at(1, 1, s), us, (T)1);
         odd_finish<T>(acc, bA, a.diag, a.scale, a.g5out);
     } else if (order_parity(a.g, s)) {
         // odd: z, t, x, y, then the centre
@@ -420,27 +356,27 @@ __device__ __forceinline__ void dslash_sites(const DslashArgs<T> &a, const LK &l
         load_site<T, G5IN>(in, V, zb, bB);
         project<T, 2, -1>(bA, h);
         load_site<T, G5IN>(in, V, tf, bA);
-        hop_h<T, 2, -1, false>(acc, h, lk.at(2, 0, s, s), us, (T)1);
+        hop_h<T, 2, -1, false>(acc, h, lk.at(2, 0, s), us, (T)1);
         project<T, 2, +1>(bB, h);
         load_site<T, G5IN>(in, V, tb, bB);
-        hop_h<T, 2, +1, true>(acc, h, lk.at(2, 1, zb, s), us, (T)1);
+        hop_h<T, 2, +1, true>(acc, h, lk.at(2, 1, s), us, (T)1);
         project<T, 3, -1>(bA, h);
         load_site<T, G5IN>(in, V, xf, bA);
-        hop_h<T, 3, -1, false>(acc, h, lk.at(3, 0, s, s), us, ff);
+        hop_h<T, 3, -1, false>(acc, h, lk.at(3, 0, s), us, ff);
         project<T, 3, +1>(bB, h);
         load_site<T, G5IN>(in, V, xb, bB);
-        hop_h<T, 3, +1, true>(acc, h, lk.at(3, 1, tb, s), us, fb);
+        hop_h<T, 3, +1, true>(acc, h, lk.at(3, 1, s), us, fb);
         project<T, 0, -1>(bA, h);
         load_site<T, G5IN>(in, V, yf, bA);
-        hop_h<T, 0, -1, false>(acc, h, lk.at(0, 0, s, s), us, (T)1);
+        hop_h<T, 0, -1, false>(acc, h, lk.at(0, 0, s), us, (T)1);
         project<T, 0, +1>(bB, h);
         load_site<T, G5IN>(in, V, yb, bB);
-        hop_h<T, 0, +1, true>(acc, h, lk.at(0, 1, xb, s), us, (T)1);
+        hop_h<T, 0, +1, true>(acc, h, lk.at(0, 1, s), us, (T)1);
         project<T, 1, -1>(bA, h);
         load_site<T, G5IN>(in, V, s, bA);    // the centre, for the diagonal term
-        hop_h<T, 1, -1, false>(acc, h, lk.at(1, 0, s, s), us, (T)1);
+        hop_h<T, 1, -1, false>(acc, h, lk.at(1, 0, s), us, (T)1);
         project<T, 1, +1>(bB, h);
-        hop_h<T, 1, +1, true>(acc, h, lk.at(1, 1, yb, s), us, (T)1);
+        hop_h<T, 1, +1, true>(acc, h, lk.at(1, 1, s), us, (T)1);
         odd_finish<T>(acc, bA, a.diag, a.scale, a.g5out);
     } else {
         // even: the centre, x, y, z, t
@@ -451,11 +387,11 @@ __device__ __forceinline__ void dslash_sites(const DslashArgs<T> &a, const LK &l
             diag_start<T>(acc, bB, (T)-2 * a.diag);
             project<T, 0, -1>(bB, h);
             x_rotate<T, true>(h);
-            hop_h<T, 0, -1, false>(acc, h, lk.at(0, 0, s, s), us, (T)1);
+            hop_h<T, 0, -1, false>(acc, h, lk.at(0, 0, s), us, (T)1);
             project<T, 0, +1>(bB, h);
             load_site<T, G5IN>(in, V, yb, bB);
             x_rotate<T, false>(h);
-            hop_h<T, 0, +1, true>(acc, h, lk.at(0, 1, xb, s), us, (T)1);
+            hop_h<T, 0, +1, true>(acc, h, lk.at(0, 1, s), us, (T)1);
         } else {
             C<T> cc[12];
             load_site<T, G5IN>(in, V, s, cc);
@@ -464,29 +400,28 @@ __device__ __forceinline__ void dslash_sites(const DslashArgs<T> &a, const LK &l
             diag_start<T>(acc, cc, (T)-2 * a.diag);
             project<T, 0, -1>(bA, h);
             load_site<T, G5IN>(in, V, yf, bA);
-            hop_h<T, 0, -1, false>(acc, h, lk.at(0, 0, s, s), us, (T)1);
+            hop_h<T, 0, -1, false>(acc, h, lk.at(0, 0, s), us, (T)1);
             project<T, 0, +1>(bB, h);
             load_site<T, G5IN>(in, V, yb, bB);
-            hop_h<T, 0, +1, true>(acc, h, lk.at(0, 1, xb, s), us, (T)1);
+            hop_h<T, 0, +1, true>(acc, h, lk.at(0, 1, s), us, (T)1);
         }
         project<T, 1, -1>(bA, h);
         load_site<T, G5IN>(in, V, zf, bA);
-        hop_h<T, 1, -1, false>(acc, h, lk.at(1, 0, s, s), us, (T)1);
+        hop_h<T, 1, -1, false>(acc, h, lk.at(1, 0, s), us, (T)1);
         project<T, 1, +1>(bB, h);
         load_site<T, G5IN>(in, V, zb, bB);
-        hop_h<T, 1, +1, true>(acc, h, lk.at(1, 1, yb, s), us, (T)1);
+        hop_h<T, 1, +1, true>(acc, h, lk.at(1, 1, s), us, (T)1);
         project<T, 2, -1>(bA, h);
         load_site<T, G5IN>(in, V, tf, bA);
-        hop_h<T, 2, -1, false>(acc, h, lk.at(2, 0, s, s), us, (T)1);
+        hop_h<T, 2, -1, false>(acc, h, lk.at(2, 0, s), us, (T)1);
         project<T, 2, +1>(bB, h);
         load_site<T, G5IN>(in, V, tb, bB);
-        hop_h<T, 2, +1, true>(acc, h, lk.at(2, 1, zb, s), us, (T)1);
+        hop_h<T, 2, +1, true>(acc, h, lk.at(2, 1, s), us, (T)1);
         project<T, 3, -1>(bA, h);
-        hop_h<T, 3, -1, false>(acc, h, lk.at(3, 0, s, s), us, ff);
+        hop_h<T, 3, -1, false>(acc, h, lk.at(3, 0, s), us, ff);
         project<T, 3, +1>(bB, h);
-        hop_h<T, 3, +1, true>(acc, h, lk.at(3, 1, tb, s), us, fb);
+        hop_h<T, 3, +1, true>(acc, h, lk.at(3, 1, s), us, fb);
         even_finish<T>(acc, a.scale, a.g5out);
-    }
     }
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp) {
@@ -494,35 +429,26 @@ __device__ __forceinline__ void dslash_sites(const DslashArgs<T> &a, const LK &l
         for (int c = 0; c < 3; ++c) {
             const int k = 3 * sp + c;
             C<T> o = acc[sp][c];
-            if (EPI != EPI_PLAIN) o = cadd(o, cscale(ld_stream<LK::staged>(v, k, V, s), sig0));
-            if (EPI == EPI_SV2) o = csub(o, ld_stream<LK::staged>(wsub, k, V, s));
-            if constexpr (LK::staged) {
-                // streamed past L2: the output is not read again by this
-                // sweep, and its lines would evict neighbour spinors
-                C<T> &d = elem_at<true>(out, k, V, s);
-                __builtin_nontemporal_store(o.x, &d.x);
-                __builtin_nontemporal_store(o.y, &d.y);
-            } else {
-                elem_at<false>(out, k, V, s) = o;
-            }
+            if (EPI != EPI_PLAIN) o = cadd(o, cscale(ld_stream(v, k, V, s), sig0));
+            if (EPI == EPI_SV2) o = csub(o, ld_stream(wsub, k, V, s));
+            // streamed past L2: the output is not read again by this sweep,
+            // and its lines would evict neighbour spinors
+            C<T> &d = elem(out, k, V, s);
+            __builtin_nontemporal_store(o.x, &d.x);
+            __builtin_nontemporal_store(o.y, &d.y);
             if (EPI == EPI_MV) {
-                const C<T> r = ld_stream<LK::staged>(rt, k, V, s);
-                part[0] += (double)r.x * o.x + (double)r.y * o.y;
-                part[1] += (double)r.x * o.y - (double)r.y * o.x;
+                const C<T> r = ld_stream(rt, k, V, s);
+                part[0] += dot_re(r, o);
+                part[1] += dot_im(r, o);
             }
             // EPI_MVN: no r~ here, its dot comes from a sparse list
-            if (epi_dots(EPI)) part[2] += (double)o.x * o.x + (double)o.y * o.y;
+            if (epi_dots(EPI)) part[2] += norm2(o);
             if (EPI == EPI_MV_Y) {
-                double2 &yr = elem_at<LK::staged>(y, k, V, s);
-                double2 yv = ld_stream<LK::staged>(y, k, V, s);
-                yv.x += (double)yc.x * o.x - (double)yc.y * o.y;
-                yv.y += (double)yc.x * o.y + (double)yc.y * o.x;
-                if constexpr (LK::staged) {
-                    __builtin_nontemporal_store(yv.x, &yr.x);
-                    __builtin_nontemporal_store(yv.y, &yr.y);
-                } else {
-                    yr = yv;
-                }
+                double2 &yr = elem(y, k, V, s);
+                double2 yv = ld_stream(y, k, V, s);
+                yv = cadd(yv, ymul(yc, o));
+                __builtin_nontemporal_store(yv.x, &yr.x);
+                __builtin_nontemporal_store(yv.y, &yr.y);
             }
         }
     }
@@ -554,33 +480,6 @@ __device__ __forceinline__ RhsOps<T> rhs_ops(const DslashArgs<T> &a, int rhs) {
     o.sig0 = a.sigma0_rhs ? (T)a.sigma0_rhs[rhs] : a.sigma0;
     o.w = a.w ? a.w + (size_t)rhs * (a.w_rs ? a.w_rs : nv) : nullptr;
     return o;
-}
-
-// Site-block stencil: one block per (256-site block, right-hand side), links
-// read from global memory.  Partials: one per 64-site chunk (wavefront).
-template <typename T, int EPI, bool G5IN>
-__device__ __forceinline__ void dslash_site_block(const DslashArgs<T> &a, int sblk, int rhs) {
-    if (!gate_open(a.gate, rhs)) return;
-    const RhsOps<T> o = rhs_ops<T, EPI>(a, rhs);
-    const GlobalLinks<T> lk{a.U, a.g.V};
-    double part[3] = {0.0, 0.0, 0.0};
-    dslash_sites<T, EPI, G5IN>(a, lk, o.in, o.out, o.v, o.rt, o.y, o.yc, o.sig0, o.w, sblk * BLOCK + threadIdx.x,
-                              part);
-    if (epi_dots(EPI))
-        wave_reduce_store<3>(part, a.part + (size_t)rhs * PMAX * a.ps + sblk * (BLOCK / 64) + (threadIdx.x >> 6),
-                             a.ps);
-}
-
-// Block p of the flattened grid (8 per blocks) to (site block, rhs): hardware
-// block p runs on XCD p % 8, which owns the contiguous logical range
-// [(p % 8) per, (p % 8 + 1) per); inside it the right-hand side varies
-// fastest, so the sources of one site block run back to back on one XCD.
-template <typename T, int EPI, bool G5IN>
-__device__ __forceinline__ void dslash_body(const DslashArgs<T> &a, int p) {
-    const int L = (p & 7) * a.per + (p >> 3);
-    if (L >= a.nsb * a.nrhs) return;
-    const int sblk = L / a.nrhs;
-    dslash_site_block<T, EPI, G5IN>(a, sblk, L - sblk * a.nrhs);
 }
 
 // Site offset of the backward neighbour in direction nu.
@@ -656,6 +555,189 @@ __device__ __forceinline__ void dslash_chunk(const DslashArgs<T> &a, int p) {
         dslash_sites<T, EPI, G5IN>(a, lk, o.in, o.out, o.v, o.rt, o.y, o.yc, o.sig0, o.w, base + lane, part);
         if (epi_dots(EPI)) wave_reduce_store<3>(part, a.part + (size_t)rhs * PMAX * a.ps + chunk, a.ps);
     }
+}
+
+// g = U h (U^+ h with DAG) for a link held in registers, with hop_h's
+// arithmetic.
+template <typename T, bool DAG>
+__device__ __forceinline__ void link_mul(const C<T> (&u)[9], const C<T> (&h)[2][3], C<T> (&g)[2][3]) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            C<T> r;
+            if (!DAG) {
+                r = cmul(u[3 * a], h[i][0]);
+                r = cfma(u[3 * a + 1], h[i][1], r);
+                r = cfma(u[3 * a + 2], h[i][2], r);
+            } else {
+                r = cmulc(u[a], h[i][0]);
+                r = cadd(r, cmulc(u[3 + a], h[i][1]));
+                r = cadd(r, cmulc(u[6 + a], h[i][2]));
+            }
+            g[i][a] = r;
+        }
+}
+
+// LDS of a block of the split stencil: the hops' products [8 hops][6][CHUNK]
+// and, for the partials, the output and r~ [12][CHUNK].
+template <typename T, int EPI>
+struct SplitLds {
+    C<T> g[8 * 6 * CHUNK];
+    C<T> o[epi_dots(EPI) ? 12 * CHUNK : 1];
+    C<T> r[EPI == EPI_MV ? 12 * CHUNK : 1];
+};
+
+// The part of wavefront NU of a block of the split stencil: both hops of
+// direction NU, then spin NU of the output.
+template <typename T, int EPI, bool G5IN, int NU>
+__device__ __forceinline__ void split_wave(const DslashArgs<T> &a, SplitLds<T, EPI> &lds, int chunk, int rhs) {
+    const int lane = threadIdx.x & 63;
+    const int V = a.g.V, Lt = a.g.Lt;
+    const int s_ = chunk * CHUNK + lane;
+    const bool valid = s_ < V;
+    const int s = valid ? s_ : V - 1;   // lanes past the lattice repeat its last site and store nothing
+    const int d = NU == 0 ? 1 : NU == 1 ? a.g.Lx : NU == 2 ? a.g.Lx * a.g.Ly : a.g.Lx * a.g.Ly * a.g.Lz;
+    const int L = NU == 0 ? a.g.Lx : NU == 1 ? a.g.Ly : NU == 2 ? a.g.Lz : Lt;
+    const int xn = NU == 3 ? s / d : (s / d) % L;
+    const int sf = xn == L - 1 ? s - (L - 1) * d : s + d;
+    const int sb = xn == 0 ? s + (L - 1) * d : s - d;
+    const int t = NU == 3 ? xn : s / (a.g.Lx * a.g.Ly * a.g.Lz);
+    const RhsOps<T> o = rhs_ops<T, EPI>(a, rhs);
+    C<T> bF[12], bB[12], uF[9], uB[9];
+    const C<T> *U = a.U + (size_t)NU * 9 * (unsigned)V;
+    load_site<T, G5IN>(o.in, V, sf, bF);
+#pragma unroll
+    for (int e = 0; e < 9; ++e) uF[e] = elem(U, e, V, s);
+    load_site<T, G5IN>(o.in, V, sb, bB);
+#pragma unroll
+    for (int e = 0; e < 9; ++e) uB[e] = elem(U, e, V, sb);
+    // what spin NU's output needs besides the hops
+    C<T> cen[3], vv[3], rr[3], ww[3];
+    double2 yy[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const int k = 3 * NU + c;
+        cen[c] = elem(o.in, k, V, s);
+        if (G5IN && NU >= 2) cen[c] = cneg(cen[c]);
+        if (EPI != EPI_PLAIN) vv[c] = elem(o.v, k, V, s);
+        if (EPI == EPI_SV2) ww[c] = elem(o.w, k, V, s);
+        if (EPI == EPI_MV) rr[c] = elem(o.rt, k, V, s);
+        if (EPI == EPI_MV_Y) yy[c] = elem(o.y, k, V, s);
+    }
+    C<T> h[2][3], gF[2][3], gB[2][3];
+    project<T, NU, -1>(bF, h);
+    link_mul<T, false>(uF, h, gF);
+    project<T, NU, +1>(bB, h);
+    link_mul<T, true>(uB, h, gB);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            lds.g[((2 * NU) * 6 + 3 * i + c) * CHUNK + lane] = gF[i][c];
+            lds.g[((2 * NU + 1) * 6 + 3 * i + c) * CHUNK + lane] = gB[i][c];
+        }
+    __syncthreads();
+    const T ff = (t == Lt - 1) ? a.ef * a.bc : a.ef;
+    const T fb = (t == 0) ? a.eb * a.bc : a.eb;
+    // acc + f * (spin NU, colour c of the hop in direction N, backward with B)
+    auto add = [&](auto N_, auto B_, int c, C<T> acc) __attribute__((always_inline)) {
+        constexpr int N = decltype(N_)::value, B = decltype(B_)::value;
+        using P = Proj<N, B ? 1 : -1>;
+        constexpr int i = NU < 2 ? NU : (NU == 2 ? P::Q2 : P::Q3);
+        C<T> g = N == NU ? (B ? gB[i][c] : gF[i][c]) : lds.g[((2 * N + B) * 6 + 3 * i + c) * CHUNK + lane];
+        if (NU == 2) g = mulcode<P::D2>(g);
+        if (NU == 3) g = mulcode<P::D3>(g);
+        return cadd(acc, cscale(g, N == 3 ? (B ? fb : ff) : (T)1));
+    };
+    auto both = [&](auto N_, int c, C<T> acc) __attribute__((always_inline)) {
+        acc = add(N_, std::integral_constant<int, 0>{}, c, acc);
+        return add(N_, std::integral_constant<int, 1>{}, c, acc);
+    };
+    constexpr std::integral_constant<int, 0> X{};
+    constexpr std::integral_constant<int, 1> Y{};
+    constexpr std::integral_constant<int, 2> Z{};
+    constexpr std::integral_constant<int, 3> Ti{};
+    C<T> out[3];
+    if (order_parity(a.g, s)) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) out[c] = both(Y, c, both(X, c, both(Ti, c, both(Z, c, mk<T>(0, 0)))));
+        odd_finish_spin<T>(out, cen, a.diag, ((a.g5out && NU >= 2) ? (T)-1 : (T)1) * a.scale);
+    } else {
+        diag_start_spin<T>(out, cen, (T)-2 * a.diag);
+        const T f = ((a.g5out && NU >= 2) ? (T)0.5 : (T)-0.5) * a.scale;
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            out[c] = cscale(both(Ti, c, both(Z, c, both(Y, c, both(X, c, out[c])))), f);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const int k = 3 * NU + c;
+        C<T> z = out[c];
+        if (EPI != EPI_PLAIN) z = cadd(z, cscale(vv[c], o.sig0));
+        if (EPI == EPI_SV2) z = csub(z, ww[c]);
+        if (valid) elem(o.out, k, V, s) = z;
+        if (EPI == EPI_MV_Y) {
+            double2 yv = yy[c];
+            yv = cadd(yv, ymul(o.yc, z));
+            if (valid) elem(o.y, k, V, s) = yv;
+        }
+        if (epi_dots(EPI)) {
+            lds.o[k * CHUNK + lane] = z;
+            if (EPI == EPI_MV) lds.r[k * CHUNK + lane] = rr[c];
+        }
+    }
+    if (epi_dots(EPI)) {
+        // wavefronts 0, 1, 2 sum ||out||^2, Re and Im <rt, out>: per lane over
+        // the components in the other forms' order, then over the lanes
+        __syncthreads();
+        if (NU == 3) return;
+        constexpr int row = NU == 0 ? 2 : NU - 1;
+        double x = 0.0;
+        if ((NU == 0 || EPI == EPI_MV) && valid) {
+#pragma unroll
+            for (int k = 0; k < 12; ++k) {
+                const C<T> z = lds.o[k * CHUNK + lane];
+                if (NU == 0) x += norm2(z);
+                if constexpr (EPI == EPI_MV) {
+                    const C<T> r = lds.r[k * CHUNK + lane];
+                    if (NU == 1) x += dot_re(r, z);
+                    if (NU == 2) x += dot_im(r, z);
+                }
+            }
+        }
+        x = wave_sum(x);
+        if (lane == 0) a.part[(size_t)rhs * PMAX * a.ps + row * a.ps + chunk] = x;
+    }
+}
+
+// Split stencil, for launches that cannot fill the chip with one lane per
+// site (dslash_use_split): one block of four wavefronts per 64-site chunk and
+// right-hand side.  A lane per site gathers its nine spinors and eight links
+// in a chain of dependent trips to memory; here wavefront nu does both hops of
+// direction nu, with its 24 spinor and 18 link loads and spin nu's epilogue
+// operands all in flight at once, passes the products U h through LDS and
+// finishes spin nu, adding the hops in the other forms' order with their
+// arithmetic (the same bits).  What bounds it is one trip to memory, a barrier
+// and the launch where the lattice is small, the links' traffic where it is
+// large (one right-hand side moves 36 complex of links per site for 24 of
+// spinor).  A lane per site against this form, FP64, one right-hand side:
+// 4^3x8 9.9 -> 5.1 us, 12^3x24 17 -> 10.5, 24^3x48 (637 MB) 221 -> 155; with
+// r~ and partials 11.3 -> 5.6, 19.7 -> 13.3, 262 -> 200.  Its output and
+// epilogue operands use cached accesses: up to 16^3x32 the vectors of one
+// right-hand side stay in the caches from one launch to the next.
+template <typename T, int EPI, bool G5IN>
+__device__ __forceinline__ void dslash_split(const DslashArgs<T> &a, int p) {
+    __shared__ SplitLds<T, EPI> lds;
+    const int i = p >> 3;
+    const int slot = i / a.nrhs, rhs = i - slot * a.nrhs;
+    const int chunk = slab_chunk(a, p & 7, slot);
+    if (chunk < 0 || !gate_open(a.gate, rhs)) return;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w == 0) split_wave<T, EPI, G5IN, 0>(a, lds, chunk, rhs);
+    else if (w == 1) split_wave<T, EPI, G5IN, 1>(a, lds, chunk, rhs);
+    else if (w == 2) split_wave<T, EPI, G5IN, 2>(a, lds, chunk, rhs);
+    else split_wave<T, EPI, G5IN, 3>(a, lds, chunk, rhs);
 }
 
 }  // namespace dev
