@@ -256,6 +256,46 @@ __device__ inline void block_sum_rows(const double *p, long stride, const int *r
     for (int r = 0; r < NR; ++r) out[r] = res[r];
 }
 
+// block_sum_rows for a block of NT >= BLOCK work-items (the one-launch scalar
+// stages, whose time is the trips of these loads): each wavefront takes whole
+// (row, quarter) pieces, the part of a row that wavefront `quarter` of a
+// 256-wide block would add, so a row's loads are all in flight over four
+// wavefronts and the rows do not wait for each other.  The same sums in the
+// same order, bit for bit.
+template <int NT, int NR>
+__device__ inline void block_sum_rows_wide(const double *p, long stride, const int *rows, int cnt, int n,
+                                           double (&out)[NR]) {
+    static_assert(BLOCK == 256, "a row is four wavefronts' sums");
+    __shared__ double sh[NR][BLOCK / 64];
+    constexpr int U = 16;
+    const int lane = threadIdx.x & 63;
+    __syncthreads();   // a caller may sum again
+    for (int task = threadIdx.x >> 6; task < cnt * 4; task += NT / 64) {
+        const double *pr = p + (size_t)rows[task >> 2] * stride;
+        double x = 0.0;
+        for (int i = (task & 3) * 64 + lane; i < n; i += U * BLOCK) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = i + u * BLOCK < n ? pr[i + u * BLOCK] : 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) x += v[u];
+        }
+        x = wave_sum(x);
+        if (lane == 0) sh[task >> 2][task & 3] = x;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        double t = 0.0;
+        if (r < cnt) {
+            t = sh[r][0];
+#pragma unroll
+            for (int w = 1; w < BLOCK / 64; ++w) t += sh[r][w];
+        }
+        out[r] = t;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Device-resident solver state (one per right-hand side) and the per-step
 // coefficient tables that the scalar kernels write and the vector kernels

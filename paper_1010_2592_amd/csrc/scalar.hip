@@ -29,14 +29,17 @@ namespace {
 using namespace dev;
 
 __global__ __launch_bounds__(BLOCK) void sc_init(ScalarArgs a) { sc_init_body(a, blockIdx.x); }
-__global__ __launch_bounds__(BLOCK) void sc_beta(ScalarArgs a) { sc_beta_body(a, blockIdx.x); }
-__global__ __launch_bounds__(BLOCK) void sc_alpha(ScalarArgs a) { sc_alpha_body(a, blockIdx.x); }
-__global__ __launch_bounds__(BLOCK) void sc_mr(ScalarArgs a) { sc_mr_body(a, blockIdx.x); }
-__global__ __launch_bounds__(BLOCK) void sc_rel(ScalarArgs a) { sc_rel_body(a, blockIdx.x); }
-__global__ __launch_bounds__(BLOCK) void sc_conv(ScalarArgs a) { sc_conv_body(a, blockIdx.x); }
-__global__ __launch_bounds__(BLOCK) void sc_defer(ScalarArgs a) { sc_defer_body(a, blockIdx.x); }
+__global__ __launch_bounds__(SC_THREADS) void sc_beta(ScalarArgs a) { sc_beta_body<SC_THREADS>(a, blockIdx.x); }
+__global__ __launch_bounds__(SC_THREADS) void sc_alpha(ScalarArgs a) { sc_alpha_body<SC_THREADS>(a, blockIdx.x); }
+__global__ __launch_bounds__(SC_THREADS) void sc_mr(ScalarArgs a) { sc_mr_body<SC_THREADS>(a, blockIdx.x); }
+__global__ __launch_bounds__(SC_THREADS) void sc_rel(ScalarArgs a) { sc_rel_body<SC_THREADS>(a, blockIdx.x); }
+__global__ __launch_bounds__(SC_THREADS) void sc_conv(ScalarArgs a) { sc_conv_body<SC_THREADS>(a, blockIdx.x); }
+template <int L>
+__global__ __launch_bounds__(512) void sc_defer(ScalarArgs a) {
+    sc_defer_body<L>(a, blockIdx.x);
+}
 __global__ __launch_bounds__(BLOCK) void sc_basis(ScalarArgs a) { sc_basis_body(a, blockIdx.x); }
-__global__ __launch_bounds__(BLOCK) void sc_exh(ScalarArgs a) { sc_exh_body(a, blockIdx.x); }
+__global__ __launch_bounds__(SC_THREADS) void sc_exh(ScalarArgs a) { sc_exh_body<SC_THREADS>(a, blockIdx.x); }
 __global__ __launch_bounds__(64) void sc_basis_replay(BasisReplayArgs a) { sc_basis_replay_body(a, blockIdx.x); }
 
 }  // namespace
@@ -45,28 +48,32 @@ void launch_sc_init(hipStream_t st, const ScalarArgs &a, int nrhs) {
     hipLaunchKernelGGL(sc_init, dim3(nrhs), dim3(BLOCK), 0, st, a);
 }
 void launch_sc_beta(hipStream_t st, const ScalarArgs &a, int nrhs) {
-    hipLaunchKernelGGL(sc_beta, dim3(nrhs), dim3(BLOCK), 0, st, a);
+    hipLaunchKernelGGL(sc_beta, dim3(nrhs), dim3(SC_THREADS), 0, st, a);
 }
 void launch_sc_alpha(hipStream_t st, const ScalarArgs &a, int nrhs) {
-    hipLaunchKernelGGL(sc_alpha, dim3(nrhs), dim3(BLOCK), 0, st, a);
+    hipLaunchKernelGGL(sc_alpha, dim3(nrhs), dim3(SC_THREADS), 0, st, a);
 }
 void launch_sc_mr(hipStream_t st, const ScalarArgs &a, int nrhs) {
-    hipLaunchKernelGGL(sc_mr, dim3(nrhs), dim3(BLOCK), 0, st, a);
+    hipLaunchKernelGGL(sc_mr, dim3(nrhs), dim3(SC_THREADS), 0, st, a);
 }
 void launch_sc_rel(hipStream_t st, const ScalarArgs &a, int nrhs) {
-    hipLaunchKernelGGL(sc_rel, dim3(nrhs), dim3(BLOCK), 0, st, a);
+    hipLaunchKernelGGL(sc_rel, dim3(nrhs), dim3(SC_THREADS), 0, st, a);
 }
 void launch_sc_conv(hipStream_t st, const ScalarArgs &a, int nrhs) {
-    hipLaunchKernelGGL(sc_conv, dim3(nrhs), dim3(BLOCK), 0, st, a);
+    hipLaunchKernelGGL(sc_conv, dim3(nrhs), dim3(SC_THREADS), 0, st, a);
 }
 void launch_sc_defer(hipStream_t st, const ScalarArgs &a, int nrhs) {
-    hipLaunchKernelGGL(sc_defer, dim3(nrhs), dim3(BLOCK), 0, st, a);
+    switch (a.l) {
+#define C_(L) case L: hipLaunchKernelGGL((sc_defer<L>), dim3(nrhs), dim3(512), 0, st, a); break;
+        C_(1) C_(2) C_(3) C_(4) C_(5) C_(6) C_(7) C_(8)
+#undef C_
+    }
 }
 void launch_sc_basis(hipStream_t st, const ScalarArgs &a, int nrhs) {
     hipLaunchKernelGGL(sc_basis, dim3(nrhs), dim3(BLOCK), 0, st, a);
 }
 void launch_sc_exh(hipStream_t st, const ScalarArgs &a, int nrhs) {
-    hipLaunchKernelGGL(sc_exh, dim3(nrhs), dim3(BLOCK), 0, st, a);
+    hipLaunchKernelGGL(sc_exh, dim3(nrhs), dim3(SC_THREADS), 0, st, a);
 }
 void launch_sc_basis_replay(hipStream_t st, const BasisReplayArgs &a, int nrhs) {
     hipLaunchKernelGGL(sc_basis_replay, dim3(nrhs), dim3(64), 0, st, a);

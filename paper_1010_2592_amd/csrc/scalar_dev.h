@@ -1,6 +1,7 @@
 // Device bodies of the scalar stages of multi-shift BiCGstab(l), one block
 // per right-hand side (see scalar.hip for the recurrences).  Shared by the
-// one-launch-per-stage kernels and the persistent kernel.
+// one-launch-per-stage kernels (NT = SC_THREADS work-items) and the persistent
+// kernel (NT = BLOCK).
 #pragma once
 #include "common.h"
 #include "kernels.h"
@@ -19,15 +20,60 @@ __device__ inline const double *prow(const ScalarArgs &a, int rhs) {
     return a.part + (size_t)rhs * PMAX * a.ps;
 }
 
-// the sums of partial rows 0, 1, 2 (re, im of an inner product, a squared
-// norm) in one pass, bitwise those of three block_sum calls
+// Work-items of the one-launch scalar stages.  These kernels are a few
+// dependent trips to memory in one block per right-hand side; sixteen
+// wavefronts take the rows of partial sums side by side.
+constexpr int SC_THREADS = 1024;
+
+// sums of rows rows[0 .. cnt) of the partials, as block_sum gives each
+template <int NT, int NR>
+__device__ inline void sum_rows(const double *row, long ps, const int *rows, int cnt, int n, double (&out)[NR]) {
+    if constexpr (NT == BLOCK) block_sum_rows<NR>(row, ps, rows, cnt, n, out);
+    else block_sum_rows_wide<NT, NR>(row, ps, rows, cnt, n, out);
+}
+// the sum of one row
+template <int NT>
+__device__ inline double sum1(const double *row, int n) {
+    if constexpr (NT == BLOCK) {
+        return block_sum(row, n);
+    } else {
+        const int rows[1] = {0};
+        double o[1];
+        block_sum_rows_wide<NT, 1>(row, 0, rows, 1, n, o);
+        return o[0];
+    }
+}
+// the sums of partial rows 0, 1, 2 (re, im of an inner product, a squared norm)
+template <int NT>
 __device__ inline void sum3(const double *row, long ps, int n, double &s0, double &s1, double &s2) {
     const int rows[3] = {0, 1, 2};
     double o[3];
-    block_sum_rows<3>(row, ps, rows, 3, n, o);
+    sum_rows<NT, 3>(row, ps, rows, 3, n, o);
     s0 = o[0];
     s1 = o[1];
     s2 = o[2];
+}
+
+// min over the active shifts of |zeta psi| (1e308 without any), for wavefront
+// 0: a shift per lane (NSMAX = 64 of them), since one lane's walk over the
+// shifts' states was a chain of trips to memory
+__device__ inline double min_shift_scale(const ScalarArgs &a, const SeedState &S, int rhs) {
+    static_assert(NSMAX == 64, "one shift per lane");
+    double mn = 1e308;
+    const int q = threadIdx.x & 63;
+    if (q < S.nact) {
+        const ShiftState &H = a.sh[(size_t)rhs * NSMAX + S.act[q]];
+        if (H.active) {
+            const double sc = cmod(cmul(H.zeta, H.psi));
+            mn = sc < mn ? sc : mn;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const double o = __shfl_xor(mn, off, 64);
+        mn = o < mn ? o : mn;
+    }
+    return mn;
 }
 
 __device__ __forceinline__ void sc_init_body(const ScalarArgs &a, int rhs) {
@@ -79,31 +125,28 @@ __device__ __forceinline__ void sc_init_body(const ScalarArgs &a, int rhs) {
     }
 }
 
+template <int NT = BLOCK>
 __device__ __forceinline__ void sc_beta_body(const ScalarArgs &a, int rhs) {
     SeedState &S = a.seed[rhs];
     if (!S.run || !S.bicg_on) return;
     const int j = a.j;
     const double *row = prow(a, rhs);
-    double re, im, rj2;
-    sum3(row, a.ps, a.nblk, re, im, rj2);
-    double r02 = 0.0;
-    if (j >= 1) r02 = block_sum(row + 3 * a.ps, a.nblk2);
-    if (threadIdx.x != 0) return;
-    if (j == 0) S.wu_ready = 0;
     // basis form: ||r_0|| exists only where sc_exh found that the test could
     // fire; elsewhere it cannot (||r_0|| >= ||r_{j-1}|| / ||S||^(j-1))
     const bool have_r0 = !a.basis || S.exh_check;
+    const bool test = j >= 1 && have_r0 && !S.forced && S.nact > 0;
+    double re, im, rj2;
+    sum3<NT>(row, a.ps, a.nblk, re, im, rj2);
+    double r02 = 0.0;
+    if (j >= 1 && have_r0) r02 = sum1<NT>(row + 3 * a.ps, a.nblk2);
+    if (threadIdx.x >= 64) return;
+    const double mn = test ? min_shift_scale(a, S, rhs) : 0.0;
+    if (threadIdx.x != 0) return;
+    if (j == 0) S.wu_ready = 0;
     if (j >= 1 && have_r0) S.rnorm0 = sqrt(r02);
-    if (j >= 1 && have_r0 && !S.forced && S.nact > 0) {
+    if (test) {
         // Krylov space exhausted: every active shift already meets its
         // tolerance after the previous step's r-update
-        double mn = 1e308;
-        for (int q = 0; q < S.nact; ++q) {
-            const ShiftState &H = a.sh[(size_t)rhs * NSMAX + S.act[q]];
-            if (!H.active) continue;
-            const double sc = cmod(cmul(H.zeta, H.psi));
-            mn = sc < mn ? sc : mn;
-        }
         if (S.rnorm0 <= FREEZE_FRAC * S.tol * S.bnorm * mn) {
             S.exhausted = 1;
             S.bicg_on = 0;
@@ -139,13 +182,14 @@ __device__ __forceinline__ void sc_beta_body(const ScalarArgs &a, int rhs) {
     }
 }
 
+template <int NT = BLOCK>
 __device__ __forceinline__ void sc_alpha_body(const ScalarArgs &a, int rhs) {
     SeedState &S = a.seed[rhs];
     if (!S.run || !S.bicg_on) return;
     const int j = a.j;
     const double *row = prow(a, rhs);
     double re, im, u2;
-    sum3(row, a.ps, a.nblk, re, im, u2);
+    sum3<NT>(row, a.ps, a.nblk, re, im, u2);
     __shared__ int ok;
     __shared__ double2 sh_alpha, sh_beta;
     if (threadIdx.x == 0) {
@@ -235,6 +279,7 @@ __device__ __forceinline__ void sc_alpha_body(const ScalarArgs &a, int rhs) {
     }
 }
 
+template <int NT = BLOCK>
 __device__ __forceinline__ void sc_mr_body(const ScalarArgs &a, int rhs) {
     SeedState &S = a.seed[rhs];
     if (!S.run) return;
@@ -256,37 +301,85 @@ __device__ __forceinline__ void sc_mr_body(const ScalarArgs &a, int rhs) {
         for (int ii = 0; ii < i; ++ii) p += l + 1 - ii;
         return p + (k - i);
     };
-    // the pairs (i, k) in the Gram kernel's order, 4 pairs (8 partial rows)
-    // per pass over the partials (more would cost the persistent kernel, which
-    // inlines this body, an occupancy step)
-    constexpr int NB = 4;
-    int pi_[NB], pk_[NB], rows[2 * NB];
-    int cnt = 0;
-    for (int i = 0; i <= L; ++i) {
-        for (int k = (i == 0 ? 1 : i); k <= L; ++k) {
-            pi_[cnt] = i;
-            pk_[cnt] = k;
-            rows[2 * cnt] = 2 * pidx(i, k);
-            rows[2 * cnt + 1] = 2 * pidx(i, k) + 1;
-            ++cnt;
-            const bool last = i == L && k == L;
-            if (cnt == NB || last) {
-                double sums[2 * NB];
-                block_sum_rows<2 * NB>(row, a.ps, rows, 2 * cnt, a.nblk, sums);
-                if (threadIdx.x == 0) {
-                    for (int q = 0; q < cnt; ++q) {
-                        const double re = sums[2 * q], im = sums[2 * q + 1];
-                        if (pi_[q] == 0) {
-                            cvec[pk_[q] - 1] = d2(re, -im);   // <r_k, r_0> = conj(<r_0, r_k>)
-                        } else {
-                            G[pi_[q] - 1][pk_[q] - 1] = d2(re, im);
-                            G[pk_[q] - 1][pi_[q] - 1] = d2(re, -im);
+    if constexpr (NT == BLOCK) {
+        // the pairs (i, k) in the Gram kernel's order, 4 pairs (8 partial rows)
+        // per pass over the partials (more would cost the persistent kernel, which
+        // inlines this body, an occupancy step)
+        constexpr int NB = 4;
+        int pi_[NB], pk_[NB], rows[2 * NB];
+        int cnt = 0;
+        for (int i = 0; i <= L; ++i) {
+            for (int k = (i == 0 ? 1 : i); k <= L; ++k) {
+                pi_[cnt] = i;
+                pk_[cnt] = k;
+                rows[2 * cnt] = 2 * pidx(i, k);
+                rows[2 * cnt + 1] = 2 * pidx(i, k) + 1;
+                ++cnt;
+                const bool last = i == L && k == L;
+                if (cnt == NB || last) {
+                    double sums[2 * NB];
+                    block_sum_rows<2 * NB>(row, a.ps, rows, 2 * cnt, a.nblk, sums);
+                    if (threadIdx.x == 0) {
+                        for (int q = 0; q < cnt; ++q) {
+                            const double re = sums[2 * q], im = sums[2 * q + 1];
+                            if (pi_[q] == 0) {
+                                cvec[pk_[q] - 1] = d2(re, -im);   // <r_k, r_0> = conj(<r_0, r_k>)
+                            } else {
+                                G[pi_[q] - 1][pk_[q] - 1] = d2(re, im);
+                                G[pk_[q] - 1][pi_[q] - 1] = d2(re, -im);
+                            }
                         }
                     }
+                    cnt = 0;
                 }
-                cnt = 0;
             }
         }
+    } else {
+        // every pair at once: a wavefront per piece of a row (at most 44 pairs)
+        constexpr int NPX = (LMAX + 1) * (LMAX + 2) / 2;
+        __shared__ double sh[2 * NPX][4];
+        const int lane = threadIdx.x & 63, np = (L + 1) * (L + 2) / 2;
+        for (int task = threadIdx.x >> 6; task < 8 * np; task += NT / 64) {
+            // pair number -> (i, k) over 0..L, its row in the kernel's numbering over 0..l
+            int i = 0, q = task >> 3;
+            while (q > L - i) {
+                q -= L + 1 - i;
+                ++i;
+            }
+            if (i == 0 && q == 0) continue;   // ||r_0||^2 is not part of the system
+            const double *pr = row + (size_t)(2 * pidx(i, i + q) + ((task >> 2) & 1)) * a.ps;
+            double x = 0.0;
+            constexpr int UP = 4;
+            for (int e = (task & 3) * 64 + lane; e < a.nblk; e += UP * BLOCK) {
+                double v[UP];
+#pragma unroll
+                for (int u = 0; u < UP; ++u) v[u] = e + u * BLOCK < a.nblk ? pr[e + u * BLOCK] : 0.0;
+#pragma unroll
+                for (int u = 0; u < UP; ++u) x += v[u];
+            }
+            x = wave_sum(x);
+            if (lane == 0) sh[task >> 2][task & 3] = x;
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < np) {
+            int i = 0, q = threadIdx.x;
+            while (q > L - i) {
+                q -= L + 1 - i;
+                ++i;
+            }
+            const int k = i + q;
+            if (k > 0) {
+                const double *s0 = sh[2 * threadIdx.x], *s1 = sh[2 * threadIdx.x + 1];
+                const double re = ((s0[0] + s0[1]) + s0[2]) + s0[3], im = ((s1[0] + s1[1]) + s1[2]) + s1[3];
+                if (i == 0) {
+                    cvec[k - 1] = d2(re, -im);   // <r_k, r_0> = conj(<r_0, r_k>)
+                } else {
+                    G[i - 1][k - 1] = d2(re, im);
+                    G[k - 1][i - 1] = d2(re, -im);
+                }
+            }
+        }
+        __syncthreads();
     }
     if (threadIdx.x == 0) {
         int n = L;
@@ -381,29 +474,33 @@ __device__ __forceinline__ void sc_mr_body(const ScalarArgs &a, int rhs) {
 // update r_0 = b - S x (FP64): when ||r_0|| has dropped below 0.1 of its
 // largest value since the last one, when any shift would freeze on the
 // recursively updated residual, or when the Krylov space looks exhausted.
+template <int NT = BLOCK>
 __device__ __forceinline__ void sc_rel_body(const ScalarArgs &a, int rhs) {
     SeedState &S = a.seed[rhs];
     if (!S.run || !S.mixed) return;
-    const double r02 = block_sum(prow(a, rhs) + 2 * a.ps, a.nblk);
-    if (threadIdx.x != 0) return;
+    const double r02 = sum1<NT>(prow(a, rhs) + 2 * a.ps, a.nblk);
+    if (threadIdx.x >= 64) return;
     const double rn = sqrt(r02);
-    if (rn > S.rmax) S.rmax = rn;
-    bool freeze = false;
-    for (int q = 0; q < S.nact; ++q) {
-        const ShiftState &H = a.sh[(size_t)rhs * NSMAX + S.act[q]];
-        if (!H.active) continue;
-        const bool due = S.forced ? (S.m + 1 >= H.force) : (rn / (cmod(cmul(H.zeta, H.psi)) * S.bnorm) <= FREEZE_FRAC * S.tol);
-        freeze = freeze || due;
+    bool due = false;
+    if ((int)threadIdx.x < S.nact) {
+        const ShiftState &H = a.sh[(size_t)rhs * NSMAX + S.act[threadIdx.x]];
+        if (H.active)
+            due = S.forced ? (S.m + 1 >= H.force)
+                           : (rn / (cmod(cmul(H.zeta, H.psi)) * S.bnorm) <= FREEZE_FRAC * S.tol);
     }
+    const bool freeze = __any(due);
+    if (threadIdx.x != 0) return;
+    if (rn > S.rmax) S.rmax = rn;
     S.rel = (rn <= 0.1 * S.rmax || freeze || S.exhausted) ? 1 : 0;
 }
 
+template <int NT = BLOCK>
 __device__ __forceinline__ void sc_conv_body(const ScalarArgs &a, int rhs) {
     SeedState &S = a.seed[rhs];
     if (!S.run) return;
     const double *row = prow(a, rhs);
     double re, im, r02;
-    sum3(row, a.ps, a.nblk, re, im, r02);
+    sum3<NT>(row, a.ps, a.nblk, re, im, r02);
     __shared__ double rn;
     if (threadIdx.x == 0) {
         rn = sqrt(r02);
@@ -439,22 +536,29 @@ __device__ __forceinline__ void sc_conv_body(const ScalarArgs &a, int rhs) {
         }
     }
     __syncthreads();
+    // the shifts still active, in their order: a shift per lane of wavefront 0
+    if (threadIdx.x >= 64) return;
+    const int s = threadIdx.x;
+    bool live = false, brk = false;
+    if (s < S.nshift) {
+        const ShiftState &H = a.sh[(size_t)rhs * NSMAX + s];
+        live = H.active;
+        brk = H.broken;
+    }
+    const unsigned long long lv = __ballot(live);
+    const int nact = __popcll(lv);
+    const bool anybroken = __any(brk);
+    if (live) S.act[__popcll(lv & ((1ull << s) - 1ull))] = s;
+    const bool ends = S.broken || S.exhausted || (S.m + 1 >= S.max_outer);
+    if (live && ends) a.sh[(size_t)rhs * NSMAX + s].iters = S.m + 1;
     if (threadIdx.x == 0) {
-        int nact = 0, anybroken = 0;
-        for (int s = 0; s < S.nshift; ++s) {
-            const ShiftState &H = a.sh[(size_t)rhs * NSMAX + s];
-            if (H.active) S.act[nact++] = s;
-            anybroken |= H.broken;
-        }
         S.nact = nact;
         S.m += 1;
         S.rel = 0;
-        const bool stop = (nact == 0) || S.broken || S.exhausted || (S.m >= S.max_outer);
-        if (stop) {
+        if (nact == 0 || ends) {
             S.run = 0;
             if (nact > 0) {
                 S.status = S.broken ? S_BREAKDOWN : S_NOT_CONVERGED;
-                for (int q = 0; q < nact; ++q) a.sh[(size_t)rhs * NSMAX + S.act[q]].iters = S.m;
             } else {
                 S.status = anybroken ? S_BREAKDOWN : S_OK;
             }
@@ -468,70 +572,80 @@ __device__ __forceinline__ void sc_conv_body(const ScalarArgs &a, int rhs) {
 }
 
 // Deferred single pass: every active shift's update over the outer iteration
-// that just ended, as coefficients on the iteration's basis (see DeferCoef).
-// One work-item per shift replays the iteration on coefficient vectors: the
-// seed's r_i, u_i exactly as the vector kernels updated them (the recorded
+// that just ended, as coefficients on the iteration's basis (see DeferCoef):
+// the seed's r_i, u_i exactly as the vector kernels updated them (the recorded
 // beta, alpha and step flags), and the shift's u^s_i and x^s increment by the
 // recurrences of the per-step form (the recorded step coefficients of every
 // step and the MR coefficients).  Vectors no step defined are zero, as the
-// per-step form multiplies their stale contents by zero coefficients.
+// per-step form multiplies their stale contents by zero coefficients.  The
+// recurrences act on each basis index alone: one work-item per (shift, index)
+// with its column of each in registers.  One work-item per shift, its arrays
+// in scratch memory, took 107 us a launch at l = 4 with 16 shifts.
+template <int L>
 __device__ __forceinline__ void sc_defer_body(const ScalarArgs &a, int rhs) {
     SeedState &S = a.seed[rhs];
     if (!S.run) return;
-    const int l = a.l, nb = 2 * l + 2, self = nb;
-    for (int q = threadIdx.x; q < S.nact; q += BLOCK) {
+    constexpr int nb = 2 * L + 2, self = nb;
+    for (int item = threadIdx.x; item < S.nact * NDEF; item += blockDim.x) {
+        const int q = item / NDEF, b = item - q * NDEF;
         DeferCoef &d = a.dc[(size_t)rhs * NSMAX + q];
-        d.s = S.act[q];
-        double2 R[LMAX + 1][NDEF], U[LMAX + 1][NDEF], w[LMAX + 1][NDEF], dx[NDEF];
-        for (int i = 0; i <= l; ++i)
-            for (int b = 0; b <= nb; ++b) R[i][b] = U[i][b] = w[i][b] = d2(0, 0);
-        for (int b = 0; b <= nb; ++b) dx[b] = d2(0, 0);
-        R[0][0] = d2(1, 0);
-        U[0][1] = d2(1, 0);
-        w[0][self] = d2(1, 0);
-        bool live = true;
-        for (int j = 0; j < l; ++j) {
-            const int flag = S.step_flag[j];
-            if (flag == 0) break;
+        if (b == 0) {
+            d.s = S.act[q];
+            d.live = 1;
+        }
+        if (b > nb) {
+            d.cu[b] = d.cx[b] = d2(0, 0);
+            continue;
+        }
+        double2 R[L + 1], U[L + 1], w[L + 1], dx = d2(0, 0);
+#pragma unroll
+        for (int i = 0; i <= L; ++i) R[i] = U[i] = w[i] = d2(0, 0);
+        if (b == 0) R[0] = d2(1, 0);
+        if (b == 1) U[0] = d2(1, 0);
+        if (b == self) w[0] = d2(1, 0);
+        bool live = true, on = true;   // on: the iteration's steps have not ended
+#pragma unroll
+        for (int j = 0; j < L; ++j) {
+            const int flag = on ? S.step_flag[j] : 0;
+            if (flag == 0) {
+                on = false;
+                continue;
+            }
             const double2 beta = S.step_beta[j];
-            for (int i = 0; i <= j; ++i)
-                for (int b = 0; b <= nb; ++b) U[i][b] = csub(R[i][b], cmul(beta, U[i][b]));
-            for (int b = 0; b <= nb; ++b) U[j + 1][b] = d2(0, 0);
-            U[j + 1][2 + 2 * j] = d2(1, 0);
-            if (flag == 1) break;
-            const StepCoef c = a.sc_hist[((size_t)rhs * LMAX + j) * NSMAX + q];
+#pragma unroll
+            for (int i = 0; i <= j; ++i) U[i] = csub(R[i], cmul(beta, U[i]));
+            U[j + 1] = b == 2 + 2 * j ? d2(1, 0) : d2(0, 0);
+            if (flag == 1) {
+                on = false;
+                continue;
+            }
+            const StepCoef &c = a.sc_hist[((size_t)rhs * LMAX + j) * NSMAX + q];
             if (live && c.live) {
-                for (int i = 0; i <= j; ++i)
-                    for (int b = 0; b <= nb; ++b) w[i][b] = csub(cmul(c.kap, R[i][b]), cmul(c.beta_s, w[i][b]));
-                for (int b = 0; b <= nb; ++b) dx[b] = cfma(c.alpha_s, w[0][b], dx[b]);
-                for (int b = 0; b <= nb; ++b)
-                    w[j + 1][b] = csub(cadd(cmul(c.a1, R[j][b]), cmul(c.a2, U[j + 1][b])), cscale(w[j][b], c.sp));
+#pragma unroll
+                for (int i = 0; i <= j; ++i) w[i] = csub(cmul(c.kap, R[i]), cmul(c.beta_s, w[i]));
+                dx = cfma(c.alpha_s, w[0], dx);
+                w[j + 1] = csub(cadd(cmul(c.a1, R[j]), cmul(c.a2, U[j + 1])), cscale(w[j], c.sp));
             } else {
                 live = false;
             }
             const double2 alpha = S.step_alpha[j];
-            for (int i = 0; i <= j; ++i)
-                for (int b = 0; b <= nb; ++b) R[i][b] = csub(R[i][b], cmul(alpha, U[i + 1][b]));
-            for (int b = 0; b <= nb; ++b) R[j + 1][b] = d2(0, 0);
-            R[j + 1][3 + 2 * j] = d2(1, 0);
+#pragma unroll
+            for (int i = 0; i <= j; ++i) R[i] = csub(R[i], cmul(alpha, U[i + 1]));
+            R[j + 1] = b == 3 + 2 * j ? d2(1, 0) : d2(0, 0);
         }
         const MRCoef &m = a.mc[(size_t)rhs * NSMAX + q];
         if (live && m.live) {
-            for (int k = 0; k < l; ++k)
-                for (int b = 0; b <= nb; ++b) dx[b] = cfma(m.kc[k], R[k][b], dx[b]);
-            for (int b = 0; b <= nb; ++b) {
-                double2 u0 = w[0][b];
-                for (int i = 1; i <= l; ++i) u0 = csub(u0, cmul(S.gam[i - 1], w[i][b]));
-                w[0][b] = cmul(u0, m.inv_q);
-            }
+#pragma unroll
+            for (int k = 0; k < L; ++k) dx = cfma(m.kc[k], R[k], dx);
+            double2 u0 = w[0];
+#pragma unroll
+            for (int i = 1; i <= L; ++i) u0 = csub(u0, cmul(S.gam[i - 1], w[i]));
+            w[0] = cmul(u0, m.inv_q);
         }
         // a shift whose recurrences stopped this iteration keeps the part
         // applied before: the per-step form updated it until then
-        for (int b = 0; b < NDEF; ++b) {
-            d.cu[b] = b <= nb ? w[0][b] : d2(0, 0);
-            d.cx[b] = b <= nb ? dx[b] : d2(0, 0);
-        }
-        d.live = 1;
+        d.cu[b] = w[0];
+        d.cx[b] = dx;
     }
 }
 
@@ -628,6 +742,7 @@ __device__ __forceinline__ void sc_basis_replay_body(const BasisReplayArgs &a, i
 // twice that factor of the test's threshold, exh_check is set and r_0's
 // coefficients are written for the kernel that forms it; otherwise the test
 // cannot fire and is left out.
+template <int NT>
 __device__ __forceinline__ void sc_exh_body(const ScalarArgs &a, int rhs) {
     SeedState &S = a.seed[rhs];
     if (!S.run || !S.bicg_on) {
@@ -636,19 +751,14 @@ __device__ __forceinline__ void sc_exh_body(const ScalarArgs &a, int rhs) {
     }
     const int j = a.j;
     const double *row = prow(a, rhs);
-    const double rj1 = sqrt(block_sum(row + 4 * a.ps, a.nblk2));
+    const double rj1 = sqrt(sum1<NT>(row + 4 * a.ps, a.nblk2));
     __shared__ int check;
     __shared__ double2 R[LMAX + 1][NBB], U[LMAX + 1][NBB];
+    const bool test = !S.forced && S.nact > 0;
+    const double mn = (threadIdx.x < 64 && test) ? min_shift_scale(a, S, rhs) : 0.0;
     if (threadIdx.x == 0) {
         check = 0;
-        if (!S.forced && S.nact > 0) {
-            double mn = 1e308;
-            for (int q = 0; q < S.nact; ++q) {
-                const ShiftState &H = a.sh[(size_t)rhs * NSMAX + S.act[q]];
-                if (!H.active) continue;
-                const double sc = cmod(cmul(H.zeta, H.psi));
-                mn = sc < mn ? sc : mn;
-            }
+        if (test) {
             double fac = 2.0;
             for (int k = 0; k < j - 1; ++k) fac *= a.norm_a;
             if (rj1 <= fac * FREEZE_FRAC * S.tol * S.bnorm * mn) check = 1;
