@@ -103,79 +103,97 @@ __global__ __launch_bounds__(BLOCK) void k_cg_init(CGArgs a) {
     }
 }
 
-// alpha_k from (p_k, S p_k); each active shift's zeta_{k+1} and alpha^s_k
+// alpha_k from (p_k, S p_k); each active shift's zeta_{k+1} and alpha^s_k, a
+// shift per lane of wavefront 0 (one lane's walk over 30 shifts, a chain of
+// trips to memory, was most of this kernel's 6 us)
 __global__ __launch_bounds__(BLOCK) void k_cg_alpha(CGArgs a) {
+    static_assert(NSMAX == 64, "one shift per lane");
     const int rhs = blockIdx.x;
     CGSeed &S = a.seed[rhs];
     if (!S.run) return;
     const double pw = block_sum(cg_row(a, rhs, 0), a.nblk_ds);
-    if (threadIdx.x != 0) return;
+    if (threadIdx.x >= 64) return;
+    const int q = threadIdx.x, nact = S.nact, k = S.k;
+    const bool bad = !(pw > 0.0) || !isfinite(pw);
+    const double alpha = S.rr / pw;
+    const double d = k > 0 ? alpha * S.beta_prev / S.alpha_prev : 0.0;
+    if (q < nact) {
+        const int s = S.act[q];
+        CGShift &H = a.sh[(size_t)rhs * NSMAX + s];
+        if (bad) {
+            H.iters = k;
+        } else {
+            const double zn = (1.0 + d + alpha * H.sp) * H.zeta - d * H.zeta_prev;
+            const double as = alpha * H.zeta / zn;
+            H.zeta_next = zn;
+            H.alpha_s = as;
+            CGCoef &c = a.coef[(size_t)rhs * NSMAX + q];
+            c.inv_zeta = 1.0 / H.zeta;
+            c.beta_s = H.beta_s;
+            c.alpha_s = as;
+            c.s = s;
+            c.first = k == 0 ? 1 : 0;
+        }
+    }
+    if (q != 0) return;
     S.mv += 1;
     S.dots += 1;
-    if (!(pw > 0.0) || !isfinite(pw)) {
+    if (bad) {
         S.status = S_BREAKDOWN;
         S.run = 0;
-        for (int q = 0; q < S.nact; ++q) a.sh[(size_t)rhs * NSMAX + S.act[q]].iters = S.k;
         return;
     }
-    const double alpha = S.rr / pw;
-    const double d = S.k > 0 ? alpha * S.beta_prev / S.alpha_prev : 0.0;
     S.alpha = alpha;
-    if (a.tape_a) a.tape_a[(size_t)rhs * a.tape_stride + S.k] = alpha;
-    for (int q = 0; q < S.nact; ++q) {
-        CGShift &H = a.sh[(size_t)rhs * NSMAX + S.act[q]];
-        const double zn = (1.0 + d + alpha * H.sp) * H.zeta - d * H.zeta_prev;
-        H.zeta_next = zn;
-        H.alpha_s = alpha * H.zeta / zn;
-        CGCoef &c = a.coef[(size_t)rhs * NSMAX + q];
-        c.inv_zeta = 1.0 / H.zeta;
-        c.beta_s = H.beta_s;
-        c.alpha_s = H.alpha_s;
-        c.s = S.act[q];
-        c.first = S.k == 0 ? 1 : 0;
-    }
+    if (a.tape_a) a.tape_a[(size_t)rhs * a.tape_stride + k] = alpha;
 }
 
 // beta_k from ||r_{k+1}||^2; shift beta^s_k, residuals, freezing, termination
+// (a shift per lane of wavefront 0; the shifts still active keep their order)
 __global__ __launch_bounds__(BLOCK) void k_cg_beta(CGArgs a) {
     const int rhs = blockIdx.x;
     CGSeed &S = a.seed[rhs];
     if (!S.run) return;
     const double rrn = block_sum(cg_row(a, rhs, 3), a.nblk_v);
-    if (threadIdx.x != 0) return;
-    S.dots += 1;
+    if (threadIdx.x >= 64) return;
+    const int q = threadIdx.x, k1 = S.k + 1;
     const double beta = rrn / S.rr;
-    if (a.tape_b) a.tape_b[(size_t)rhs * a.tape_stride + S.k] = beta;
-    int nact = 0;
-    for (int q = 0; q < S.nact; ++q) {
-        const int s = S.act[q];
+    const bool last = k1 >= S.max_iter;
+    bool stays = false, brk = false;
+    int s = 0;
+    if (q < S.nact) {
+        s = S.act[q];
         CGShift &H = a.sh[(size_t)rhs * NSMAX + s];
         const double zn = H.zeta_next;
         H.beta_s = beta * (H.zeta / zn) * (H.zeta / zn);
         H.zeta_prev = H.zeta;
         H.zeta = zn;
-        H.res = sqrt(rrn) / fabs(zn) / S.bnorm;
-        const bool done = S.forced ? (S.k + 1 >= H.force) : (H.res <= FREEZE_FRAC * S.tol);
-        if (done || !isfinite(H.res)) {
-            H.active = 0;
-            H.iters = S.k + 1;
-            if (!isfinite(H.res)) S.status = S_BREAKDOWN;
-        } else {
-            S.act[nact++] = s;
-        }
+        const double res = sqrt(rrn) / fabs(zn) / S.bnorm;
+        H.res = res;
+        const bool done = S.forced ? (k1 >= H.force) : (res <= FREEZE_FRAC * S.tol);
+        brk = !isfinite(res);
+        stays = !(done || brk);
+        if (!stays) H.active = 0;
+        if (!stays || last) H.iters = k1;
     }
+    const unsigned long long lv = __ballot(stays);
+    const int nact = __popcll(lv);
+    const bool anybrk = __any(brk);
+    if (stays) S.act[__popcll(lv & ((1ull << q) - 1ull))] = s;
+    if (q != 0) return;
+    S.dots += 1;
+    if (a.tape_b) a.tape_b[(size_t)rhs * a.tape_stride + S.k] = beta;
+    if (anybrk) S.status = S_BREAKDOWN;
     S.nact = nact;
     S.alpha_prev = S.alpha;
     S.beta_prev = beta;
     S.beta = beta;
     S.rr = rrn;
-    S.k += 1;
+    S.k = k1;
     if (nact == 0) {
         S.run = 0;
-    } else if (S.k >= S.max_iter) {
+    } else if (last) {
         S.run = 0;
         if (S.status == S_OK) S.status = S_NOT_CONVERGED;
-        for (int q = 0; q < nact; ++q) a.sh[(size_t)rhs * NSMAX + S.act[q]].iters = S.k;
     }
 }
 
@@ -443,7 +461,8 @@ int solve_cg(Ctx *c, const SolveParams &P, const double2 *b, double2 *y, double2
     }
     CG_HIPCHK(hipGetLastError());
 
-    // Mv: w = a g5 D (g5 D p) + sigma0 p with (p, w) partials
+    // Mv: w = a g5 D (g5 D p) + sigma0 p with (p, w) partials (real: S is
+    // Hermitian), p read once for both
     Gate g_run;
     g_run.flag = &seed[0].run;
     g_run.flag_stride = (long)sizeof(CGSeed) / (long)sizeof(int);
@@ -456,14 +475,13 @@ int solve_cg(Ctx *c, const SolveParams &P, const double2 *b, double2 *y, double2
     d2.in = tmp;
     d2.out = w;
     d2.v = p;
-    d2.rt = p;
     d2.scale = P.a_scale;
     d2.sigma0_rhs = (const double *)c->ws_sig0.p;
     d2.part = part;
     d2.ps = ps;
     d2.gate = g_run;
     const double ds_plain = nrhs * 24 * cB * Vd + 36 * cB * Vd;
-    const double ds_mv = nrhs * 48 * cB * Vd + 36 * cB * Vd;
+    const double ds_mv = nrhs * 36 * cB * Vd + 36 * cB * Vd;
     CGVec vv;
     vv.seed = seed;
     vv.coef = ca.coef;
@@ -486,7 +504,7 @@ int solve_cg(Ctx *c, const SolveParams &P, const double2 *b, double2 *y, double2
         }
         {
             Prof pr(c, CL_STENCIL, ds_mv);
-            launch_dslash<double>(st, d2, nrhs, EPI_MV, false);
+            launch_dslash<double>(st, d2, nrhs, EPI_MVV, false);
         }
         {
             Prof pr(c, CL_SCALAR, 0);

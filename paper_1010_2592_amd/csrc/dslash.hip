@@ -25,6 +25,8 @@
 //   EPI_MVN    as EPI_MV without reading rt (partials of
 //              <rt, out> left zero; the solver adds them from a sparse list
 //              of rt's nonzero entries)
+//   EPI_MVV    as EPI_MV with rt = v and partials of Re <v, out> alone (the
+//              CG step's (p, S p)): v is read once
 // Which operands exist is a compile-time property of the mode: run-time null
 // checks inside the unrolled epilogue made the compiler keep every epilogue
 // load live at once and spill.
@@ -207,6 +209,7 @@ void launch_dslash(hipStream_t st, DslashArgs<T> a, int nrhs, int epi, bool g5in
     else if (epi == EPI_SV) launch_form<T, EPI_SV, false>(st, a, nrhs);
     else if (epi == EPI_SV2) launch_form<T, EPI_SV2, false>(st, a, nrhs);
     else if (epi == EPI_MVN) launch_form<T, EPI_MVN, false>(st, a, nrhs);
+    else if (epi == EPI_MVV) launch_form<T, EPI_MVV, false>(st, a, nrhs);
     else launch_form<T, EPI_MV_Y, false>(st, a, nrhs);
 }
 

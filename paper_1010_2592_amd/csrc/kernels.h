@@ -5,10 +5,10 @@
 
 namespace msb {
 
-enum { EPI_PLAIN = 0, EPI_MV = 1, EPI_MV_Y = 2, EPI_SV = 3, EPI_MVN = 5, EPI_SV2 = 7 };
+enum { EPI_PLAIN = 0, EPI_MV = 1, EPI_MV_Y = 2, EPI_SV = 3, EPI_MVV = 4, EPI_MVN = 5, EPI_SV2 = 7 };
 // epilogues that write partials (EPI_MVN: EPI_MV without the <r~, out> term,
-// which a sparse list supplies)
-__host__ __device__ constexpr bool epi_dots(int e) { return e == EPI_MV || e == EPI_MVN; }
+// which a sparse list supplies; EPI_MVV: Re <v, out> in row 0 alone)
+__host__ __device__ constexpr bool epi_dots(int e) { return e == EPI_MV || e == EPI_MVN || e == EPI_MVV; }
 
 // A per-right-hand-side complex coefficient in device memory: the value for
 // rhs r is *(const double2 *)(p + r * stride).

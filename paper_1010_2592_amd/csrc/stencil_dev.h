@@ -429,7 +429,11 @@ __device__ __forceinline__ void dslash_sites(const DslashArgs<T> &a, const LdsLi
         for (int c = 0; c < 3; ++c) {
             const int k = 3 * sp + c;
             C<T> o = acc[sp][c];
-            if (EPI != EPI_PLAIN) o = cadd(o, cscale(ld_stream(v, k, V, s), sig0));
+            C<T> vk;
+            if (EPI != EPI_PLAIN) {
+                vk = ld_stream(v, k, V, s);
+                o = cadd(o, cscale(vk, sig0));
+            }
             if (EPI == EPI_SV2) o = csub(o, ld_stream(wsub, k, V, s));
             // streamed past L2: the output is not read again by this sweep,
             // and its lines would evict neighbour spinors
@@ -441,8 +445,9 @@ __device__ __forceinline__ void dslash_sites(const DslashArgs<T> &a, const LdsLi
                 part[0] += dot_re(r, o);
                 part[1] += dot_im(r, o);
             }
+            if (EPI == EPI_MVV) part[0] += dot_re(vk, o);
             // EPI_MVN: no r~ here, its dot comes from a sparse list
-            if (epi_dots(EPI)) part[2] += norm2(o);
+            else if (epi_dots(EPI)) part[2] += norm2(o);
             if (EPI == EPI_MV_Y) {
                 double2 &yr = elem(y, k, V, s);
                 double2 yv = ld_stream(y, k, V, s);
@@ -553,7 +558,9 @@ __device__ __forceinline__ void dslash_chunk(const DslashArgs<T> &a, int p) {
         const RhsOps<T> o = rhs_ops<T, EPI>(a, rhs);
         double part[3] = {0.0, 0.0, 0.0};
         dslash_sites<T, EPI, G5IN>(a, lk, o.in, o.out, o.v, o.rt, o.y, o.yc, o.sig0, o.w, base + lane, part);
-        if (epi_dots(EPI)) wave_reduce_store<3>(part, a.part + (size_t)rhs * PMAX * a.ps + chunk, a.ps);
+        double *prow = a.part + (size_t)rhs * PMAX * a.ps + chunk;
+        if (EPI == EPI_MVV) wave_reduce_store<1>({part[0]}, prow, a.ps);
+        else if (epi_dots(EPI)) wave_reduce_store<3>(part, prow, a.ps);
     }
 }
 
@@ -580,12 +587,12 @@ __device__ __forceinline__ void link_mul(const C<T> (&u)[9], const C<T> (&h)[2][
 }
 
 // LDS of a block of the split stencil: the hops' products [8 hops][6][CHUNK]
-// and, for the partials, the output and r~ [12][CHUNK].
+// and, for the partials, the output and r~ (EPI_MVV: v) [12][CHUNK].
 template <typename T, int EPI>
 struct SplitLds {
     C<T> g[8 * 6 * CHUNK];
     C<T> o[epi_dots(EPI) ? 12 * CHUNK : 1];
-    C<T> r[EPI == EPI_MV ? 12 * CHUNK : 1];
+    C<T> r[EPI == EPI_MV || EPI == EPI_MVV ? 12 * CHUNK : 1];
 };
 
 // The part of wavefront NU of a block of the split stencil: both hops of
@@ -685,21 +692,23 @@ __device__ __forceinline__ void split_wave(const DslashArgs<T> &a, SplitLds<T, E
         if (epi_dots(EPI)) {
             lds.o[k * CHUNK + lane] = z;
             if (EPI == EPI_MV) lds.r[k * CHUNK + lane] = rr[c];
+            if (EPI == EPI_MVV) lds.r[k * CHUNK + lane] = vv[c];
         }
     }
     if (epi_dots(EPI)) {
         // wavefronts 0, 1, 2 sum ||out||^2, Re and Im <rt, out>: per lane over
         // the components in the other forms' order, then over the lanes
         __syncthreads();
-        if (NU == 3) return;
+        if (NU == 3 || (EPI == EPI_MVV && NU != 1)) return;
         constexpr int row = NU == 0 ? 2 : NU - 1;
         double x = 0.0;
-        if ((NU == 0 || EPI == EPI_MV) && valid) {
+        constexpr bool dots = EPI == EPI_MV || EPI == EPI_MVV;
+        if ((NU == 0 || dots) && valid) {
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
                 const C<T> z = lds.o[k * CHUNK + lane];
                 if (NU == 0) x += norm2(z);
-                if constexpr (EPI == EPI_MV) {
+                if constexpr (dots) {
                     const C<T> r = lds.r[k * CHUNK + lane];
                     if (NU == 1) x += dot_re(r, z);
                     if (NU == 2) x += dot_im(r, z);
