@@ -303,9 +303,9 @@ template <int L>
 __global__ __launch_bounds__(BLOCK) void k_basis_gram(BasisArgs<double> a) {
     basis_gram_body<L>(a, blockIdx.x, gridDim.x, blockIdx.y);
 }
-template <int L>
+template <int L, bool SHIFTS>
 __global__ __launch_bounds__(BLOCK) void k_basis_mr_update(BasisArgs<double> a) {
-    basis_mr_update_body<L>(a, blockIdx.x, gridDim.x, blockIdx.y);
+    basis_mr_update_body<L, SHIFTS>(a, blockIdx.x, gridDim.x, blockIdx.y);
 }
 template <int L>
 __global__ __launch_bounds__(64) void k_basis_spec(BasisArgs<double> a) {
@@ -621,13 +621,18 @@ void launch_basis_gram(hipStream_t st, const BasisArgs<double> &a, int nrhs, int
 #undef C_
     }
 }
-void launch_basis_mr_update(hipStream_t st, const BasisArgs<double> &a, int nrhs, int nblk) {
-    dim3 g(nblk, nrhs), b(BLOCK);
+template <bool SHIFTS>
+static void basis_mr_update_l(hipStream_t st, const BasisArgs<double> &a, dim3 g, dim3 b) {
     switch (a.l) {
-#define C_(L) case L: hipLaunchKernelGGL((k_basis_mr_update<L>), g, b, 0, st, a); break;
+#define C_(L) case L: hipLaunchKernelGGL((k_basis_mr_update<L, SHIFTS>), g, b, 0, st, a); break;
         C_(1) C_(2) C_(3) C_(4) C_(5) C_(6) C_(7) C_(8)
 #undef C_
     }
+}
+void launch_basis_mr_update(hipStream_t st, const BasisArgs<double> &a, bool shifts, int nrhs, int nblk) {
+    dim3 g(nblk, nrhs), b(BLOCK);
+    if (shifts) basis_mr_update_l<true>(st, a, g, b);
+    else basis_mr_update_l<false>(st, a, g, b);
 }
 void launch_basis_spec(hipStream_t st, const BasisArgs<double> &a, int nrhs) {
     switch (a.l) {

@@ -382,8 +382,16 @@ __device__ __forceinline__ void basis_gram_body(const BasisArgs<double> &a, int 
 // The MR update: r_0 = r_0 - sum_i gamma_i r_i and u_0 = u_0 - sum_i gamma_i u_i
 // (i = 1 .. l_mr), formed from the basis with the combined coefficients and
 // written over B_0 and B_1; partials <r~, r_0> (rows 0, 1; left at zero for
-// the sparse list) and ||r_0||^2 (row 2)
-template <int L>
+// the sparse list) and ||r_0||^2 (row 2).
+//
+// SHIFTS (deferred single pass): the same sweep rewrites every active shift's
+// u^s_0 and x^s over the outer iteration from the basis values it holds
+// (coefficients of sc_defer), before r_0 and u_0 overwrite B_0 and B_1.  As a
+// kernel of its own that update read the 2l + 2 basis vectors again, and
+// B_0, B_1 from a copy made at the start of the iteration: 14 of the 43
+// vector passes per outer iteration at l = 4 with 4 active shifts (12
+// sources, 16^3x32: 731 + 1498 + 198 us for MR update, shifts and copy).
+template <int L, bool SHIFTS>
 __device__ __forceinline__ void basis_mr_update_body(const BasisArgs<double> &a, int bx, int gx, int rhs) {
     if (!gate_open(a.gate, rhs)) return;
     constexpr int NBL = 2 * L + 2;
@@ -403,6 +411,19 @@ __device__ __forceinline__ void basis_mr_update_body(const BasisArgs<double> &a,
     }
     __syncthreads();
     const int nbu = basis_used(S);
+    // SHIFTS: the basis vectors this outer iteration wrote, an Mv output of a
+    // step that ended after it included; the slots after them hold whatever
+    // an earlier call left
+    int nbw = 2;
+    if (SHIFTS)
+        for (int j = 0; j < L; ++j) {
+            const int f = S.step_flag[j];
+            if (f >= 1) nbw = 3 + 2 * j;
+            if (f == 2) nbw = 4 + 2 * j;
+            if (f < 2) break;
+        }
+    const int nact = SHIFTS ? S.nact : 0;
+    const DeferCoef *dc = SHIFTS ? a.dc + (size_t)rhs * NSMAX : nullptr;
     const long n = a.n;
     double2 *R0 = a.R0 + (size_t)rhs * a.r0_rs, *U0 = a.U0 + (size_t)rhs * a.u0_rs;
     const double2 *rt = a.rt ? a.rt + (size_t)rhs * n : nullptr;
@@ -420,7 +441,7 @@ __device__ __forceinline__ void basis_mr_update_body(const BasisArgs<double> &a,
         asm volatile("" ::: "memory");   // coefficients from LDS in every pass (as in the Gram kernel)
         double2 B[NBL];
 #pragma unroll
-        for (int b = 0; b < NBL; ++b) B[b] = b < nbu ? bvec(a, b, rhs, e) : d2(0, 0);
+        for (int b = 0; b < NBL; ++b) B[b] = b < (SHIFTS ? nbw : nbu) ? bvec(a, b, rhs, e) : d2(0, 0);
         double2 r0 = d2(0, 0), u0 = d2(0, 0);
 #pragma unroll
         for (int b = 0; b < NBL; ++b) {
@@ -436,6 +457,32 @@ __device__ __forceinline__ void basis_mr_update_body(const BasisArgs<double> &a,
             part[1] += t.x * r0.y - t.y * r0.x;
         }
         part[2] += r0.x * r0.x + r0.y * r0.y;
+        if (SHIFTS) {
+            auto upd = [&](const DeferCoef &d, size_t o, double2 u0s, double2 x0) __attribute__((always_inline)) {
+                double2 un = cmul(d.cu[NBL], u0s), xn = cfma(d.cx[NBL], u0s, x0);
+#pragma unroll
+                for (int b = 0; b < NBL; ++b) {
+                    un = cfma(d.cu[b], B[b], un);
+                    xn = cfma(d.cx[b], B[b], xn);
+                }
+                a.W0[o] = un;
+                a.X[o] = xn;
+            };
+            // two shifts at a time: their four loads issue together
+            int q = 0;
+            for (; q + 1 < nact; q += 2) {
+                const DeferCoef &d0 = dc[q], &d1 = dc[q + 1];
+                const size_t o0 = ((size_t)rhs * a.nshift + d0.s) * n + e, o1 = ((size_t)rhs * a.nshift + d1.s) * n + e;
+                const double2 w0 = a.W0[o0], w1 = a.W0[o1], x0 = a.X[o0], x1 = a.X[o1];
+                upd(d0, o0, w0, x0);
+                upd(d1, o1, w1, x1);
+            }
+            if (q < nact) {
+                const DeferCoef &d = dc[q];
+                const size_t o = ((size_t)rhs * a.nshift + d.s) * n + e;
+                upd(d, o, a.W0[o], a.X[o]);
+            }
+        }
     }
     block_reduce_store<3>(part, a.part + (size_t)rhs * PMAX * a.ps + bx, a.ps);
 }

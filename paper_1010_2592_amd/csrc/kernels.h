@@ -237,6 +237,11 @@ struct BasisArgs {
     const double2 *sp_val = nullptr;  // [rhs][sp_max]
     const int *sp_cnt = nullptr;      // [rhs], at most SPARSE_MAX
     int sp_max = 0;
+    // deferred single pass: the shifts' vectors, updated by the MR update
+    C<T> *W0 = nullptr;               // [rhs][nshift][n] u^s_0 of every shift
+    double2 *X = nullptr;             // [rhs][nshift][n] shift solutions
+    const DeferCoef *dc = nullptr;    // [rhs][NSMAX]
+    int nshift = 0;
 };
 void launch_basis_axpy(hipStream_t, const BasisArgs<double> &, int nrhs, int nblk);
 // replay of the double pass in basis form: r_0, u_0 after outer iteration
@@ -245,7 +250,8 @@ void launch_basis_axpy(hipStream_t, const BasisArgs<double> &, int nrhs, int nbl
 void launch_basis_combine(hipStream_t, const BasisArgs<double> &, int nrhs, int nblk);
 void launch_basis_r0norm(hipStream_t, const BasisArgs<double> &, int nrhs, int nblk);
 void launch_basis_gram(hipStream_t, const BasisArgs<double> &, int nrhs, int nblk);
-void launch_basis_mr_update(hipStream_t, const BasisArgs<double> &, int nrhs, int nblk);
+// shifts: also every active shift's update over the outer iteration
+void launch_basis_mr_update(hipStream_t, const BasisArgs<double> &, bool shifts, int nrhs, int nblk);
 // sparse r~: <r~, r_0> after the MR step and the next iteration's beta, from
 // the basis before the MR update (one block per right-hand side)
 void launch_basis_spec(hipStream_t, const BasisArgs<double> &, int nrhs);

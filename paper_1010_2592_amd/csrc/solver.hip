@@ -719,10 +719,10 @@ struct Emit {
             launch_basis_gram(st, a, nrhs, nblk);
         }
     }
-    void basis_mr_update(const BasisArgs<double> &a, int nrhs, int nblk, int cls, double bytes) {
+    void basis_mr_update(const BasisArgs<double> &a, bool shifts, int nrhs, int nblk, int cls, double bytes) {
         if (launching(cls, bytes)) {
             Prof p(c, cls, bytes);
-            launch_basis_mr_update(st, a, nrhs, nblk);
+            launch_basis_mr_update(st, a, shifts, nrhs, nblk);
         }
     }
     void basis_spec(const BasisArgs<double> &a, int nrhs) {
@@ -1213,8 +1213,9 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
         VecArgs<T> v = va;
         ScalarArgs s = sa;
         DslashArgs<T> e1 = d1, e2 = d2;
-        if (deferred) {
-            // the iteration's basis starts with r_0 and u_0
+        if (deferred && !basis) {
+            // the iteration's basis starts with r_0 and u_0 (in the seed's
+            // basis form they stay in place until the MR update)
             v.gate = g_run;
             e.snapshot(v, nrhs, nbv, CL_SHIFT, nr_run * 4.0 * nd * cB);
         }
@@ -1226,7 +1227,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
         const long store_rs = pass3 ? ps_rs : (long)nb * n;
         auto slot = [&](int t) {
             return pass3 ? (C<T> *)c->pstore[m / PSC].p + ((size_t)(m % PSC) * 2 * l + t) * n
-                         : Bm + (size_t)(2 + t) * n;
+                         : Bm + (size_t)(nb - 2 * l + t) * n;
         };
         auto from_store = [&](VecArgs<T> &x, int ri, int ui) {
             x.r_src_i = (stored && ri >= 1) ? ri : -1;
@@ -1373,18 +1374,20 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                     e.basis_spec(bm, nrhs);
                     bm.wu = WU;
                 }
-                // 2l + 2 basis vectors read, r_0 and u_0 written, and r~ read
-                // (dense) or the next u_0 update written (sparse)
-                e.basis_mr_update(bm, nrhs, nbv, CL_SEED, nr_run * (2.0 * l + 5) * nd * cB);
-                if (sparse_rt && !sa.spec) sparse_dot_of(e, R, g_run, nr_run, vs);
                 if (deferred) {
-                    // every shift's update over the iteration from the basis
-                    // (B_0, B_1 from the snapshot: the MR update has just
-                    // overwritten r_0 and u_0)
+                    // every shift's update over the iteration, on the same sweep
                     e.scalar(OP_SC_DEFER, s, nrhs);
-                    v.gate = g_run;
-                    e.defer_update(v, nrhs, nbv, CL_SHIFT_MR, nr_run * nb * nd * cB + nsh_act * (2.0 * cB + 32.0) * nd);
+                    bm.W0 = W;
+                    bm.X = X;
+                    bm.dc = (const DeferCoef *)c->ws_dc.p;
+                    bm.nshift = ns;
                 }
+                // 2l + 2 basis vectors read, r_0 and u_0 written, and r~ read
+                // (dense) or the next u_0 update written (sparse); each active
+                // shift's u^s_0 and x^s read and written
+                e.basis_mr_update(bm, deferred, nrhs, nbv, deferred ? CL_SHIFT_MR : CL_SEED,
+                                  nr_run * (2.0 * l + 5) * nd * cB + (deferred ? nsh_act * (2.0 * cB + 32.0) * nd : 0.0));
+                if (sparse_rt && !sa.spec) sparse_dot_of(e, R, g_run, nr_run, vs);
                 e.scalar(OP_SC_CONV, s, nrhs);
                 return;
             }
