@@ -51,6 +51,7 @@ struct Ctx {
     DevBuf ws_ones;
     void *host_pinned = nullptr;
     size_t host_pinned_bytes = 0;
+    hipEvent_t look[2] = {};   // ends of the last two outer iterations (see solve_impl)
     // set for the duration of a no-allocation call: device workspace comes
     // from the arena and host staging from ordinary (pageable) heap memory
     Arena *arena = nullptr;

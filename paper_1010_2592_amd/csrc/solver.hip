@@ -17,9 +17,9 @@
 // the same y as the paper's closed-form coefficients (A_mj ... G_mj, x_BiCG)
 // in a different bookkeeping; no shift vector is ever stored.
 //
-// Every inner-iteration decision is taken on the device (scalar kernels), so
-// the host synchronises once per outer iteration to learn whether any
-// right-hand side is still running.
+// Every inner-iteration decision is taken on the device (scalar kernels); the
+// host waits once per outer iteration to learn whether any right-hand side is
+// still running, with the next iteration already launched.
 #include <algorithm>
 #include <cmath>
 #include <complex>
@@ -279,6 +279,8 @@ void ctx_destroy(Ctx *c) {
     if (c->host_pinned) (void)hipHostFree(c->host_pinned);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     c->ev_pool.clear();
+    for (hipEvent_t e : c->look)
+        if (e) (void)hipEventDestroy(e);
 }
 
 // ---------------------------------------------------------------------------
@@ -911,7 +913,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
     if (!P.persistent)
         CHK(ensure(c, c->ws_sp, (size_t)nrhs * (SPMAX * (sizeof(long) + sizeof(double2)) + (1 + NBL) * sizeof(int)) +
                                     256));
-    CHK(ensure_host(c, std::max((size_t)nrhs * sizeof(SeedState), (size_t)ps * sizeof(double))));
+    CHK(ensure_host(c, std::max((size_t)2 * nrhs * sizeof(SeedState), (size_t)ps * sizeof(double))));
 
     C<T> *R = (C<T> *)c->ws_R.p, *Uv = (C<T> *)c->ws_U.p, *tmp = (C<T> *)c->ws_tmp.p;
     double *part = (double *)c->ws_part.p;
@@ -1493,7 +1495,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
         e.scalar(OP_SC_CONV, s, nrhs);
     };
 
-    CHK(ensure_host(c, (size_t)nrhs * sizeof(SeedState)));
+    CHK(ensure_host(c, (size_t)2 * nrhs * sizeof(SeedState)));   // two iterations' states
     SeedState *hseed = (SeedState *)c->host_pinned;
     if (P.persistent) {
         // the whole first pass in one cooperative launch
@@ -1503,10 +1505,23 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
         persist_ops1.swap(ops);
         CHK(run_persistent<T>(c, persist_ops1, max_outer, true, l, seed, nrhs, nullptr));
     } else {
-        int nr_run = nrhs;                       // right-hand sides still iterating
+        // The host learns after each outer iteration whether any right-hand
+        // side still runs.  It launches the next iteration before it waits
+        // for that, so the stream does not idle over the copy, the wake-up
+        // and the first launches (10 to 15 us an iteration); where nothing
+        // ran any more, the gates of the iteration launched too many are all
+        // closed.  Not where the next iteration begins with a decision on the
+        // store's memory, and not with timed launches (whose records carry
+        // the byte counts of the right-hand sides that run) or pageable
+        // staging (a call without allocations).
+        int nr_run = nrhs;                       // right-hand sides that run iteration m
         double nsh_act = (double)nrhs * ns;      // active shifts over those
+        const bool ahead = !c->prof && !c->arena;
+        if (ahead)
+            for (hipEvent_t &ev : c->look)
+                if (!ev) HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
         Emit<T> el(c, Emit<T>::LAUNCH);
-        for (int m = 0; m < max_outer; ++m) {
+        auto launch_outer = [&](int m, int nr, double nsh) -> int {
             if (pass3 && m < m_split && m % PSC == 0 && !pstore_chunk(m / PSC)) {
                 (void)hipGetLastError();
                 m_split = m;
@@ -1518,19 +1533,39 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                     HIPCHK(hipMemcpyAsync(c->ws_hs64.p, XH, (size_t)nrhs * n * sizeof(double2),
                                           hipMemcpyDeviceToDevice, st));
             }
-            emit_outer(el, nr_run, nsh_act, m);
+            emit_outer(el, nr, nsh, m);
             HIPCHK(hipGetLastError());
-            HIPCHK(hipMemcpyAsync(hseed, seed, nrhs * sizeof(SeedState), hipMemcpyDeviceToHost, st));
-            HIPCHK(hipStreamSynchronize(st));
+            HIPCHK(hipMemcpyAsync(hseed + (m & 1) * nrhs, seed, nrhs * sizeof(SeedState), hipMemcpyDeviceToHost, st));
+            if (ahead) HIPCHK(hipEventRecord(c->look[m & 1], st));
+            return 0;
+        };
+        CHK(launch_outer(0, nr_run, nsh_act));
+        for (int m = 0;; ++m) {
+            const bool more = m + 1 < max_outer;
+            bool launched = false;
+            if (ahead && more && !(pass3 && m + 1 < m_split && (m + 1) % PSC == 0)) {
+                const double bytes = c->bytes_acc;
+                CHK(launch_outer(m + 1, 0, 0));
+                c->bytes_acc = bytes;            // counted below, once it is known what runs it
+                launched = true;
+            }
+            HIPCHK(ahead ? hipEventSynchronize(c->look[m & 1]) : hipStreamSynchronize(st));
             nr_run = 0;
             nsh_act = 0;
             for (int r = 0; r < nrhs; ++r) {
-                if (hseed[r].run) {
+                const SeedState &S = hseed[(m & 1) * nrhs + r];
+                if (S.run) {
                     nr_run += 1;
-                    nsh_act += hseed[r].nact;
+                    nsh_act += S.nact;
                 }
             }
-            if (nr_run == 0) break;
+            if (nr_run == 0 || !more) break;
+            if (launched) {
+                Emit<T> ec(c, Emit<T>::COUNT);
+                emit_outer(ec, nr_run, nsh_act, m + 1);
+            } else {
+                CHK(launch_outer(m + 1, nr_run, nsh_act));
+            }
         }
     }
 
