@@ -826,6 +826,11 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
     const bool pass3 = P.pass == 3;          // pseudo-double pass: keep every Mv output
     const int nbd = (V + CHUNK - 1) / CHUNK;     // stencil partials: one per 64-site chunk
     const int nbv = nblocks_for(n);
+    // Blocks per right-hand side of the launches whose gates are nearly always
+    // closed (the exhaustion test's norm, the completion of a step that ended
+    // early): the 2048 of a streaming pass only to find the gate closed took
+    // 30 us for 12 right-hand sides
+    const int nbq = std::min(nbv, 256);
     const long ps = part_stride(c->g);
     const size_t cs = sizeof(C<T>);
     const long vs = (long)(l + 1) * n;   // rhs stride of R and U
@@ -1281,7 +1286,8 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                         BasisArgs<double> bn = ba;
                         bn.gate = g_exh;
                         bn.nbu = 2 * j + 1;
-                        e.basis_r0norm(bn, nrhs, nbv, CL_SEED, 0.0);
+                        e.basis_r0norm(bn, nrhs, nbq, CL_SEED, 0.0);
+                        s.nblk2 = nbq;
                     }
                     s.nblk = (j == 0) ? nbv : nbd;
                     e.scalar(OP_SC_BETA, s, nrhs);
@@ -1438,7 +1444,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                 vc.gate.flag_stride = (long)sizeof(SeedState) / (long)sizeof(int);
                 vc.gate.need = 1;
                 vc.gate.eq = 1;
-                e.seed_u(vc, j, nrhs, nbv, CL_SEED, 0.0, 2);
+                e.seed_u(vc, j, nrhs, nbq, CL_SEED, 0.0, 2);
             }
             // r_{j+1} = S r_j, <rt, r_{j+1}>
             e1.in = R + (size_t)j * n;
@@ -1844,7 +1850,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                     VecArgs<T> vc = vb;
                     vc.gate = gu;
                     vc.gate.eq = 1;
-                    e.seed_u(vc, j, nrhs, nbv, CL_SEED, 0.0, 2);
+                    e.seed_u(vc, j, nrhs, nbq, CL_SEED, 0.0, 2);
                 }
                 e1.in = R + (size_t)j * n;
                 e1.gate = gr;
