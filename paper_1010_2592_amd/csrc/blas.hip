@@ -308,10 +308,6 @@ __global__ __launch_bounds__(BLOCK) void k_basis_mr_update(BasisArgs<double> a) 
     basis_mr_update_body<L, SHIFTS>(a, blockIdx.x, gridDim.x, blockIdx.y);
 }
 template <int L>
-__global__ __launch_bounds__(64) void k_basis_spec(BasisArgs<double> a) {
-    basis_spec_body<L>(a, blockIdx.x);
-}
-template <int L>
 __global__ __launch_bounds__(BLOCK) void k_basis_combine(BasisArgs<double> a) {
     basis_combine_body<L>(a, blockIdx.x, gridDim.x, blockIdx.y);
 }
@@ -633,13 +629,6 @@ void launch_basis_mr_update(hipStream_t st, const BasisArgs<double> &a, bool shi
     dim3 g(nblk, nrhs), b(BLOCK);
     if (shifts) basis_mr_update_l<true>(st, a, g, b);
     else basis_mr_update_l<false>(st, a, g, b);
-}
-void launch_basis_spec(hipStream_t st, const BasisArgs<double> &a, int nrhs) {
-    switch (a.l) {
-#define C_(L) case L: hipLaunchKernelGGL((k_basis_spec<L>), dim3(nrhs), dim3(64), 0, st, a); break;
-        C_(1) C_(2) C_(3) C_(4) C_(5) C_(6) C_(7) C_(8)
-#undef C_
-    }
 }
 void launch_basis_combine(hipStream_t st, const BasisArgs<double> &a, int nrhs, int nblk) {
     dim3 g(nblk, nrhs), b(BLOCK);

@@ -487,49 +487,6 @@ __device__ __forceinline__ void basis_mr_update_body(const BasisArgs<double> &a,
     block_reduce_store<3>(part, a.part + (size_t)rhs * PMAX * a.ps + bx, a.ps);
 }
 
-// Basis form with a sparse r~, after the MR step's coefficients and before
-// the MR update overwrites r_0 and u_0: r_0 after the MR step at the list's
-// entries (the MR update's combined coefficients), <r~, r_0>, and the next
-// outer iteration's beta = alpha rho_1 / rho_0 with rho_0 <- -omega rho_0
-// (as its first step will find it), into seed_w[rhs] (one block per rhs).
-template <int L>
-__device__ __forceinline__ void basis_spec_body(const BasisArgs<double> &a, int rhs) {
-    if (!gate_open(a.gate, rhs)) return;
-    constexpr int NBL = 2 * L + 2;
-    const SeedState &S = a.seed[rhs];
-    __shared__ double2 c_r[NBL];
-    __shared__ double2 rk[SPARSE_MAX];
-    if (threadIdx.x < NBL) {
-        const int b = threadIdx.x;
-        const SeedBasis &SB = a.sb[rhs];
-        const int lm = S.l_mr < L ? S.l_mr : L;
-        double2 vr = SB.r[0][b];
-        for (int i = 1; i <= lm; ++i) vr = csub(vr, cmul(S.gam[i - 1], SB.r[i][b]));
-        c_r[b] = vr;
-    }
-    __syncthreads();
-    const int nbu = basis_used(S);
-    const int nk = a.sp_cnt[rhs];
-    if ((int)threadIdx.x < nk) {
-        const long e = a.sp_idx[(size_t)rhs * a.sp_max + threadIdx.x];
-        double2 r0 = d2(0, 0);
-        for (int b = 0; b < nbu; ++b) r0 = cfma(c_r[b], bvec(a, b, rhs, e), r0);
-        rk[threadIdx.x] = r0;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double p0 = 0.0, p1 = 0.0;
-        for (int k = 0; k < nk; ++k) {
-            const double2 t = a.sp_val[(size_t)rhs * a.sp_max + k], o = rk[k];
-            p0 += t.x * o.x + t.y * o.y;
-            p1 += t.x * o.y - t.y * o.x;
-        }
-        const double2 rho0 = cneg(cmul(S.omega, S.rho0));
-        a.seed_w[rhs].spec_rho1 = d2(p0, p1);
-        a.seed_w[rhs].beta_spec = cdiv(cmul(S.alpha, d2(p0, p1)), rho0);
-    }
-}
-
 // Replay of the double pass in basis form: r_0 and u_0 after the outer
 // iteration, written over B_0 and B_1 (no partial sums: the replay takes no
 // inner products)

@@ -252,9 +252,6 @@ void launch_basis_r0norm(hipStream_t, const BasisArgs<double> &, int nrhs, int n
 void launch_basis_gram(hipStream_t, const BasisArgs<double> &, int nrhs, int nblk);
 // shifts: also every active shift's update over the outer iteration
 void launch_basis_mr_update(hipStream_t, const BasisArgs<double> &, bool shifts, int nrhs, int nblk);
-// sparse r~: <r~, r_0> after the MR step and the next iteration's beta, from
-// the basis before the MR update (one block per right-hand side)
-void launch_basis_spec(hipStream_t, const BasisArgs<double> &, int nrhs);
 
 // mode: 0 u_0..u_j, 1 u_j only, 2 u_0..u_{j-1} (see seed_u_body)
 template <typename T> void launch_seed_u(hipStream_t, const VecArgs<T> &, int j, int nrhs, int nblk, int mode = 0);
@@ -300,14 +297,16 @@ void launch_zero(hipStream_t, C<T> *dst, long n, long stride, int nrhs);
 // a HIP error.  work: nrhs * nb ints.  Synchronises the stream.
 int sparse_list(hipStream_t, const double2 *v, long n, long rs, int nrhs, int spmax, long *idx, double2 *val,
                 int *cnt, int *work, int nb, bool fp32 = false);
-struct SparseDotArgs {
+struct SparseVec {
     const long *idx = nullptr;      // [nrhs][spmax]
     const double2 *val = nullptr;   // [nrhs][spmax]
     const int *cnt = nullptr;       // [nrhs]
     int spmax = 0;
-    const void *x = nullptr;        // the vector dotted with r~, rhs stride x_rs (elements)
+    const void *x = nullptr;        // the vector dotted with r~, rhs stride x_rs (elements); null: none
     long x_rs = 0;
     int fp32 = 0;                   // x holds float2 (mixed precision)
+};
+struct SparseDotArgs : SparseVec {
     const double2 *b = nullptr;     // set: dot with b - v instead (FP64, rhs stride x_rs)
     const double2 *v = nullptr;
     double *part = nullptr;
@@ -365,16 +364,20 @@ struct ScalarArgs {
     int spec = 0;                   // the MR update forms the next u_0 update (sparse r~)
     double norm_a = 0;              // an upper bound of ||S|| (2-norm)
     SeedBasis *sb = nullptr;        // [rhs]
+    // one-launch stages: the work of the next scalar stage on the same launch
+    SparseVec sp;                   // sc_beta (j >= 1), sc_alpha: <r~, x> from r~'s list (x set)
+    int then_beta = 0;              // sc_conv: then the next outer iteration's sc_beta (j = 0)
+    int then_basis = 0;             // sc_alpha: then sc_basis (the last step of the outer iteration)
+    int then_defer = 0;             // sc_mr: then sc_defer
 };
 
 void launch_sc_init(hipStream_t, const ScalarArgs &, int nrhs);
 void launch_sc_beta(hipStream_t, const ScalarArgs &, int nrhs);
 void launch_sc_alpha(hipStream_t, const ScalarArgs &, int nrhs);
-void launch_sc_mr(hipStream_t, const ScalarArgs &, int nrhs);
+// spec: then basis_spec (sparse r~, basis form)
+void launch_sc_mr(hipStream_t, const ScalarArgs &, const BasisArgs<double> *spec, int nrhs);
 void launch_sc_conv(hipStream_t, const ScalarArgs &, int nrhs);
 void launch_sc_rel(hipStream_t, const ScalarArgs &, int nrhs);
-void launch_sc_defer(hipStream_t, const ScalarArgs &, int nrhs);
-void launch_sc_basis(hipStream_t, const ScalarArgs &, int nrhs);
 // Replay of the double pass in basis form: outer iteration m's recorded step
 // coefficients and MR coefficients (rs [rhs][Mcap][l], ro [rhs][Mcap]) as the
 // combined coefficients of r_0 and u_0 after the iteration (sb[rhs])
@@ -407,9 +410,7 @@ enum OpKind : int {
     OP_SC_MR,
     OP_SC_REL,
     OP_SC_CONV,
-    OP_SC_DEFER,      // per-stage launches only (the deferred single pass)
-    OP_SC_BASIS,      // per-stage launches only (the basis form of the seed)
-    OP_SC_EXH,
+    OP_SC_EXH,        // per-stage launches only (the basis form of the seed)
 };
 constexpr int POP_BLOB = 512;
 struct alignas(16) POp {

@@ -30,15 +30,24 @@ using namespace dev;
 
 __global__ __launch_bounds__(BLOCK) void sc_init(ScalarArgs a) { sc_init_body(a, blockIdx.x); }
 __global__ __launch_bounds__(SC_THREADS) void sc_beta(ScalarArgs a) { sc_beta_body<SC_THREADS>(a, blockIdx.x); }
-__global__ __launch_bounds__(SC_THREADS) void sc_alpha(ScalarArgs a) { sc_alpha_body<SC_THREADS>(a, blockIdx.x); }
-__global__ __launch_bounds__(SC_THREADS) void sc_mr(ScalarArgs a) { sc_mr_body<SC_THREADS>(a, blockIdx.x); }
+__global__ __launch_bounds__(SC_THREADS) void sc_alpha(ScalarArgs a) {
+    sc_alpha_body<SC_THREADS>(a, blockIdx.x);
+    if (!a.then_basis) return;
+    __syncthreads();   // the steps' flags and coefficients, written by one work-item
+    sc_basis_body(a, blockIdx.x);
+}
+// The MR stage and what follows from its coefficients alone (512 work-items:
+// the deferred coefficients keep three columns of L + 1 in registers)
+constexpr int MR_THREADS = 512;
+template <int L>
+__global__ __launch_bounds__(MR_THREADS) void sc_mr(ScalarArgs a, BasisArgs<double> b) {
+    sc_mr_body<MR_THREADS>(a, blockIdx.x);
+    __syncthreads();
+    if (b.sp_cnt) basis_spec_body<L>(b, blockIdx.x);
+    if (a.then_defer) sc_defer_body<L>(a, blockIdx.x);
+}
 __global__ __launch_bounds__(SC_THREADS) void sc_rel(ScalarArgs a) { sc_rel_body<SC_THREADS>(a, blockIdx.x); }
 __global__ __launch_bounds__(SC_THREADS) void sc_conv(ScalarArgs a) { sc_conv_body<SC_THREADS>(a, blockIdx.x); }
-template <int L>
-__global__ __launch_bounds__(512) void sc_defer(ScalarArgs a) {
-    sc_defer_body<L>(a, blockIdx.x);
-}
-__global__ __launch_bounds__(BLOCK) void sc_basis(ScalarArgs a) { sc_basis_body(a, blockIdx.x); }
 __global__ __launch_bounds__(SC_THREADS) void sc_exh(ScalarArgs a) { sc_exh_body<SC_THREADS>(a, blockIdx.x); }
 __global__ __launch_bounds__(64) void sc_basis_replay(BasisReplayArgs a) { sc_basis_replay_body(a, blockIdx.x); }
 
@@ -53,24 +62,19 @@ void launch_sc_beta(hipStream_t st, const ScalarArgs &a, int nrhs) {
 void launch_sc_alpha(hipStream_t st, const ScalarArgs &a, int nrhs) {
     hipLaunchKernelGGL(sc_alpha, dim3(nrhs), dim3(SC_THREADS), 0, st, a);
 }
-void launch_sc_mr(hipStream_t st, const ScalarArgs &a, int nrhs) {
-    hipLaunchKernelGGL(sc_mr, dim3(nrhs), dim3(SC_THREADS), 0, st, a);
+void launch_sc_mr(hipStream_t st, const ScalarArgs &a, const BasisArgs<double> *spec, int nrhs) {
+    const BasisArgs<double> b = spec ? *spec : BasisArgs<double>{};
+    switch (a.l) {
+#define C_(L) case L: hipLaunchKernelGGL((sc_mr<L>), dim3(nrhs), dim3(MR_THREADS), 0, st, a, b); break;
+        C_(1) C_(2) C_(3) C_(4) C_(5) C_(6) C_(7) C_(8)
+#undef C_
+    }
 }
 void launch_sc_rel(hipStream_t st, const ScalarArgs &a, int nrhs) {
     hipLaunchKernelGGL(sc_rel, dim3(nrhs), dim3(SC_THREADS), 0, st, a);
 }
 void launch_sc_conv(hipStream_t st, const ScalarArgs &a, int nrhs) {
     hipLaunchKernelGGL(sc_conv, dim3(nrhs), dim3(SC_THREADS), 0, st, a);
-}
-void launch_sc_defer(hipStream_t st, const ScalarArgs &a, int nrhs) {
-    switch (a.l) {
-#define C_(L) case L: hipLaunchKernelGGL((sc_defer<L>), dim3(nrhs), dim3(512), 0, st, a); break;
-        C_(1) C_(2) C_(3) C_(4) C_(5) C_(6) C_(7) C_(8)
-#undef C_
-    }
-}
-void launch_sc_basis(hipStream_t st, const ScalarArgs &a, int nrhs) {
-    hipLaunchKernelGGL(sc_basis, dim3(nrhs), dim3(BLOCK), 0, st, a);
 }
 void launch_sc_exh(hipStream_t st, const ScalarArgs &a, int nrhs) {
     hipLaunchKernelGGL(sc_exh, dim3(nrhs), dim3(SC_THREADS), 0, st, a);

@@ -3,6 +3,7 @@
 // one-launch-per-stage kernels (NT = SC_THREADS work-items) and the persistent
 // kernel (NT = BLOCK).
 #pragma once
+#include "blas_dev.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -125,37 +126,43 @@ __device__ __forceinline__ void sc_init_body(const ScalarArgs &a, int rhs) {
     }
 }
 
-template <int NT = BLOCK>
-__device__ __forceinline__ void sc_beta_body(const ScalarArgs &a, int rhs) {
-    SeedState &S = a.seed[rhs];
-    if (!S.run || !S.bicg_on) return;
-    const int j = a.j;
-    const double *row = prow(a, rhs);
-    // basis form: ||r_0|| exists only where sc_exh found that the test could
-    // fire; elsewhere it cannot (||r_0|| >= ||r_{j-1}|| / ||S||^(j-1))
-    const bool have_r0 = !a.basis || S.exh_check;
-    const bool test = j >= 1 && have_r0 && !S.forced && S.nact > 0;
-    double re, im, rj2;
-    sum3<NT>(row, a.ps, a.nblk, re, im, rj2);
-    double r02 = 0.0;
-    if (j >= 1 && have_r0) r02 = sum1<NT>(row + 3 * a.ps, a.nblk2);
-    if (threadIdx.x >= 64) return;
-    const double mn = test ? min_shift_scale(a, S, rhs) : 0.0;
-    if (threadIdx.x != 0) return;
-    if (j == 0) S.wu_ready = 0;
-    if (j >= 1 && have_r0) S.rnorm0 = sqrt(r02);
-    if (test) {
-        // Krylov space exhausted: every active shift already meets its
-        // tolerance after the previous step's r-update
-        if (S.rnorm0 <= FREEZE_FRAC * S.tol * S.bnorm * mn) {
-            S.exhausted = 1;
-            S.bicg_on = 0;
-            S.l_eff = j;
-            return;
-        }
+// <r~, x> from the list of r~'s nonzero entries, each product formed in FP64
+// as the dense epilogues do (every work-item walks the list: at most
+// SPARSE_MAX entries)
+template <typename X>
+__device__ inline double2 sparse_sum(const SparseVec &v, int rhs) {
+    double p0 = 0.0, p1 = 0.0;
+    const int nk = v.cnt[rhs];
+    for (int k = 0; k < nk; ++k) {
+        const double2 t = v.val[(size_t)rhs * v.spmax + k];
+        const X z = reinterpret_cast<const X *>(v.x)[(size_t)rhs * v.x_rs + v.idx[(size_t)rhs * v.spmax + k]];
+        p0 += t.x * (double)z.x + t.y * (double)z.y;
+        p1 += t.x * (double)z.y - t.y * (double)z.x;
     }
-    if (j == 0) S.rho0 = cneg(cmul(S.omega, S.rho0));
-    const double2 rho1 = d2(re, im);
+    return d2(p0, p1);
+}
+// sum3, with <r~, x> from the list where the stage has one (the rows 0 and 1
+// are zero then): a launch of its own for that took 4.7 us after every Mv
+template <int NT>
+__device__ inline void dot_sums(const ScalarArgs &a, int rhs, double &re, double &im, double &n2) {
+    const double *row = prow(a, rhs);
+    if (NT != BLOCK && a.sp.x) {
+        const double2 d = a.sp.fp32 ? sparse_sum<float2>(a.sp, rhs) : sparse_sum<double2>(a.sp, rhs);
+        re = d.x;
+        im = d.y;
+        n2 = sum1<NT>(row + 2 * a.ps, a.nblk);
+    } else {
+        sum3<NT>(row, a.ps, a.nblk, re, im, n2);
+    }
+}
+
+// beta of BiCG step j from rho_1 = <r~, r_j> and ||r_j||^2 (one work-item)
+__device__ __forceinline__ void beta_step(const ScalarArgs &a, SeedState &S, int rhs, int j, double2 rho1,
+                                          double rj2) {
+    if (j == 0) {
+        S.wu_ready = 0;
+        S.rho0 = cneg(cmul(S.omega, S.rho0));
+    }
     S.dots += 1;
     if ((rho1.x == 0.0 && rho1.y == 0.0) || !cfinite(rho1) ||
         cabsd(rho1) <= BREAK_REL * S.rtnorm * sqrt(rj2)) {
@@ -183,13 +190,43 @@ __device__ __forceinline__ void sc_beta_body(const ScalarArgs &a, int rhs) {
 }
 
 template <int NT = BLOCK>
-__device__ __forceinline__ void sc_alpha_body(const ScalarArgs &a, int rhs) {
+__device__ __forceinline__ void sc_beta_body(const ScalarArgs &a, int rhs) {
     SeedState &S = a.seed[rhs];
     if (!S.run || !S.bicg_on) return;
     const int j = a.j;
     const double *row = prow(a, rhs);
+    // basis form: ||r_0|| exists only where sc_exh found that the test could
+    // fire; elsewhere it cannot (||r_0|| >= ||r_{j-1}|| / ||S||^(j-1))
+    const bool have_r0 = !a.basis || S.exh_check;
+    const bool test = j >= 1 && have_r0 && !S.forced && S.nact > 0;
+    double re, im, rj2;
+    dot_sums<NT>(a, rhs, re, im, rj2);
+    double r02 = 0.0;
+    if (j >= 1 && have_r0) r02 = sum1<NT>(row + 3 * a.ps, a.nblk2);
+    if (threadIdx.x >= 64) return;
+    const double mn = test ? min_shift_scale(a, S, rhs) : 0.0;
+    if (threadIdx.x != 0) return;
+    if (j >= 1 && have_r0) S.rnorm0 = sqrt(r02);
+    if (test) {
+        // Krylov space exhausted: every active shift already meets its
+        // tolerance after the previous step's r-update
+        if (S.rnorm0 <= FREEZE_FRAC * S.tol * S.bnorm * mn) {
+            S.exhausted = 1;
+            S.bicg_on = 0;
+            S.l_eff = j;
+            return;
+        }
+    }
+    beta_step(a, S, rhs, j, d2(re, im), rj2);
+}
+
+template <int NT = BLOCK>
+__device__ __forceinline__ void sc_alpha_body(const ScalarArgs &a, int rhs) {
+    SeedState &S = a.seed[rhs];
+    if (!S.run || !S.bicg_on) return;
+    const int j = a.j;
     double re, im, u2;
-    sum3<NT>(row, a.ps, a.nblk, re, im, u2);
+    dot_sums<NT>(a, rhs, re, im, u2);
     __shared__ int ok;
     __shared__ double2 sh_alpha, sh_beta;
     if (threadIdx.x == 0) {
@@ -568,6 +605,8 @@ __device__ __forceinline__ void sc_conv_body(const ScalarArgs &a, int rhs) {
         S.l_mr = 0;
         S.partial = 0;
         for (int i = 0; i < LMAX; ++i) S.step_flag[i] = 0;
+        // the next outer iteration's first beta reads the sums this stage took
+        if (a.then_beta && S.run) beta_step(a, S, rhs, 0, d2(re, im), r02);
     }
 }
 
@@ -698,6 +737,49 @@ __device__ __forceinline__ void sc_basis_body(const ScalarArgs &a, int rhs) {
     for (int i = 0; i <= LMAX; ++i) {
         B.r[i][b] = i <= a.l ? R[i][b] : d2(0, 0);
         B.u[i][b] = i <= a.l ? U[i][b] : d2(0, 0);
+    }
+}
+
+// Basis form with a sparse r~, after the MR step's coefficients and before
+// the MR update overwrites r_0 and u_0: r_0 after the MR step at the list's
+// entries (the MR update's combined coefficients), <r~, r_0>, and the next
+// outer iteration's beta = alpha rho_1 / rho_0 with rho_0 <- -omega rho_0
+// (as its first step will find it), into seed_w[rhs] (one block per rhs).
+template <int L>
+__device__ __forceinline__ void basis_spec_body(const BasisArgs<double> &a, int rhs) {
+    if (!gate_open(a.gate, rhs)) return;
+    constexpr int NBL = 2 * L + 2;
+    const SeedState &S = a.seed[rhs];
+    __shared__ double2 c_r[NBL];
+    __shared__ double2 rk[SPARSE_MAX];
+    if (threadIdx.x < NBL) {
+        const int b = threadIdx.x;
+        const SeedBasis &SB = a.sb[rhs];
+        const int lm = S.l_mr < L ? S.l_mr : L;
+        double2 vr = SB.r[0][b];
+        for (int i = 1; i <= lm; ++i) vr = csub(vr, cmul(S.gam[i - 1], SB.r[i][b]));
+        c_r[b] = vr;
+    }
+    __syncthreads();
+    const int nbu = basis_used(S);
+    const int nk = a.sp_cnt[rhs];
+    if ((int)threadIdx.x < nk) {
+        const long e = a.sp_idx[(size_t)rhs * a.sp_max + threadIdx.x];
+        double2 r0 = d2(0, 0);
+        for (int b = 0; b < nbu; ++b) r0 = cfma(c_r[b], bvec(a, b, rhs, e), r0);
+        rk[threadIdx.x] = r0;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double p0 = 0.0, p1 = 0.0;
+        for (int k = 0; k < nk; ++k) {
+            const double2 t = a.sp_val[(size_t)rhs * a.sp_max + k], o = rk[k];
+            p0 += t.x * o.x + t.y * o.y;
+            p1 += t.x * o.y - t.y * o.x;
+        }
+        const double2 rho0 = cneg(cmul(S.omega, S.rho0));
+        a.seed_w[rhs].spec_rho1 = d2(p0, p1);
+        a.seed_w[rhs].beta_spec = cdiv(cmul(S.alpha, d2(p0, p1)), rho0);
     }
 }
 

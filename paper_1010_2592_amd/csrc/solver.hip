@@ -727,10 +727,13 @@ struct Emit {
             launch_basis_mr_update(st, a, shifts, nrhs, nblk);
         }
     }
-    void basis_spec(const BasisArgs<double> &a, int nrhs) {
+    // the MR stage (spec: then basis_spec, per-stage launches only)
+    void sc_mr(const ScalarArgs &a, const BasisArgs<double> *spec, int nrhs) {
         if (launching(CL_SCALAR, 0.0)) {
             Prof p(c, CL_SCALAR, 0);
-            launch_basis_spec(st, a, nrhs);
+            launch_sc_mr(st, a, spec, nrhs);
+        } else if (mode == RECORD) {
+            record(op(OP_SC_MR, CL_SCALAR, nrhs), a);
         }
     }
     void basis_combine(const BasisArgs<double> &a, int nrhs, int nblk, int cls, double bytes) {
@@ -749,14 +752,11 @@ struct Emit {
         if (launching(CL_SCALAR, 0.0)) {
             Prof p(c, CL_SCALAR, 0);
             switch (kind) {
-            case OP_SC_BASIS: launch_sc_basis(st, a, nrhs); break;
             case OP_SC_EXH: launch_sc_exh(st, a, nrhs); break;
             case OP_SC_BETA: launch_sc_beta(st, a, nrhs); break;
             case OP_SC_ALPHA: launch_sc_alpha(st, a, nrhs); break;
-            case OP_SC_MR: launch_sc_mr(st, a, nrhs); break;
             case OP_SC_REL: launch_sc_rel(st, a, nrhs); break;
             case OP_SC_CONV: launch_sc_conv(st, a, nrhs); break;
-            case OP_SC_DEFER: launch_sc_defer(st, a, nrhs); break;
             default: break;
             }
         } else if (mode == RECORD) {
@@ -1215,7 +1215,38 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
     // (or basis) slot only; the seed kernels read it from there until its
     // first update
     const int mv_epi = sparse_rt ? EPI_MVN : EPI_MV;
+    // the iteration's last Mv output, r_l, meets no inner product with r~
+    const int last_epi = P.persistent ? mv_epi : EPI_SV;
     const bool fuse_seed = !P.persistent;   // fused direction updates (per-stage launches)
+    // Scalar stages.  Launched one by one, each takes along what needs nothing
+    // but its own results: <r~, x> from r~'s list, the basis coefficients after
+    // the last alpha, basis_spec and the deferred coefficients after the MR
+    // stage, the next iteration's first beta after the convergence stage (up
+    // to 2 l + 5 launches of 4 to 8 us per outer iteration).
+    auto beta_stage = [&](Emit<T> &e, ScalarArgs s, int m, int j, const void *x, long x_rs) {
+        if (!P.persistent && j == 0 && m > 0) return;   // made by the previous convergence stage
+        s.nblk = (j == 0) ? nbv : nbd;
+        if (sparse_rt && j >= 1) {
+            s.sp = spa;
+            s.sp.x = x;
+            s.sp.x_rs = x_rs;
+        }
+        e.scalar(OP_SC_BETA, s, nrhs);
+    };
+    auto alpha_stage = [&](Emit<T> &e, ScalarArgs s, const void *x, long x_rs, bool then_basis) {
+        s.nblk = nbd;
+        if (sparse_rt) {
+            s.sp = spa;
+            s.sp.x = x;
+            s.sp.x_rs = x_rs;
+        }
+        s.then_basis = then_basis ? 1 : 0;
+        e.scalar(OP_SC_ALPHA, s, nrhs);
+    };
+    auto conv_stage = [&](Emit<T> &e, ScalarArgs s) {
+        s.then_beta = P.persistent ? 0 : 1;
+        e.scalar(OP_SC_CONV, s, nrhs);
+    };
     auto emit_outer = [&](Emit<T> &e, int nr_run, double nsh_act, int m) {
         VecArgs<T> v = va;
         ScalarArgs s = sa;
@@ -1289,8 +1320,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                         e.basis_r0norm(bn, nrhs, nbq, CL_SEED, 0.0);
                         s.nblk2 = nbq;
                     }
-                    s.nblk = (j == 0) ? nbv : nbd;
-                    e.scalar(OP_SC_BETA, s, nrhs);
+                    beta_stage(e, s, m, j, j == 0 ? nullptr : ba.bv[2 * j + 1], j == 0 ? 0 : ba.brs[2 * j + 1]);
                     const int xi = (j == 0) ? 0 : 2 * j + 1;   // r_j before this step
                     const int yi = (j == 0) ? 1 : 2 * j;       // u_j before this step
                     // u_j = r_j - beta u_j (at j = 0 made by the previous MR
@@ -1327,9 +1357,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                     f2.v_rs = n;
                     f2.gate = g_bicg;
                     e.ds(f2, nrhs, mv_epi, CL_STENCIL, ds_bytes(mv_epi, nr_run));
-                    if (sparse_rt) sparse_dot_of(e, f2.out, f2.gate, nr_run, f2.out_rs);
-                    s.nblk = nbd;
-                    e.scalar(OP_SC_ALPHA, s, nrhs);
+                    alpha_stage(e, s, f2.out, f2.out_rs, j == l - 1);
                     // r_j = r_j - alpha u_{j+1}, ||r_j||^2 into row 4
                     BasisArgs<double> br = ba;
                     br.gate = g_bicg;
@@ -1349,19 +1377,16 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                     f2.out = (C<T> *)ba.bv[3 + 2 * j];
                     f2.out_rs = ba.brs[3 + 2 * j];
                     f2.v = WR;
-                    e.ds(f2, nrhs, mv_epi, CL_STENCIL, ds_bytes(mv_epi, nr_run));
-                    if (sparse_rt) sparse_dot_of(e, f2.out, f2.gate, nr_run, f2.out_rs);
+                    const int r_epi = j < l - 1 ? mv_epi : last_epi;
+                    e.ds(f2, nrhs, r_epi, CL_STENCIL, ds_bytes(r_epi, nr_run));
                 }
                 // the MR step from the basis
-                s.nblk = nbv;
-                e.scalar(OP_SC_BASIS, s, nrhs);
                 const int nbg = std::min(nbv, GRAM_NBMAX);
                 BasisArgs<double> bg = ba;
                 bg.gate = g_run;
                 e.basis_gram(bg, nrhs, nbg, CL_SEED, nr_run * (2.0 * l + 1) * nd * cB);   // all but B_1
                 s.nblk = nbg;
-                e.scalar(OP_SC_MR, s, nrhs);
-                s.nblk = nbv;
+                s.then_defer = deferred ? 1 : 0;
                 BasisArgs<double> bm = ba;
                 bm.gate = g_run;
                 bm.R0 = R;
@@ -1379,12 +1404,12 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                     bm.sp_val = spa.val;
                     bm.sp_cnt = spa.cnt;
                     bm.sp_max = spa.spmax;
-                    e.basis_spec(bm, nrhs);
-                    bm.wu = WU;
                 }
+                e.sc_mr(s, sa.spec ? &bm : nullptr, nrhs);
+                s.nblk = nbv;
+                if (sa.spec) bm.wu = WU;
                 if (deferred) {
                     // every shift's update over the iteration, on the same sweep
-                    e.scalar(OP_SC_DEFER, s, nrhs);
                     bm.W0 = W;
                     bm.X = X;
                     bm.dc = (const DeferCoef *)c->ws_dc.p;
@@ -1396,15 +1421,14 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                 e.basis_mr_update(bm, deferred, nrhs, nbv, deferred ? CL_SHIFT_MR : CL_SEED,
                                   nr_run * (2.0 * l + 5) * nd * cB + (deferred ? nsh_act * (2.0 * cB + 32.0) * nd : 0.0));
                 if (sparse_rt && !sa.spec) sparse_dot_of(e, R, g_run, nr_run, vs);
-                e.scalar(OP_SC_CONV, s, nrhs);
+                conv_stage(e, s);
                 return;
             }
         }
         for (int j = 0; j < l; ++j) {
             s.j = j;
-            s.nblk = (j == 0) ? nbv : nbd;
             s.nblk2 = nbv;
-            e.scalar(OP_SC_BETA, s, nrhs);
+            beta_stage(e, s, m, j, j == 0 ? nullptr : stored ? slot(2 * j - 1) : R + (size_t)j * n, stored ? store_rs : vs);
             v.gate = g_bicg;
             from_store(v, j, j);     // r_j and u_j: this step's first update of both
             // fused form: only u_j before its Mv; u_0..u_{j-1} in the r-update
@@ -1424,9 +1448,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                 e2.out_rs = store_rs;
             }
             e.ds(e2, nrhs, mv_epi, CL_STENCIL, ds_bytes(mv_epi, nr_run));
-            if (sparse_rt) sparse_dot_of(e, e2.out, e2.gate, nr_run, stored ? store_rs : vs);
-            s.nblk = nbd;
-            e.scalar(OP_SC_ALPHA, s, nrhs);
+            alpha_stage(e, s, e2.out, stored ? store_rs : vs, false);
             v.partials = 1;
             from_store(v, j, j + 1);     // r_j (first update) and u_{j+1} (read only)
             // seed: read r_i, u_{i+1}, write r_i; shift s (per-step form): read
@@ -1453,8 +1475,8 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
             e2.out = R + (size_t)(j + 1) * n;
             e2.v = R + (size_t)j * n;
             if (stored) e2.out = slot(2 * j + 1);
-            e.ds(e2, nrhs, mv_epi, CL_STENCIL, ds_bytes(mv_epi, nr_run));
-            if (sparse_rt) sparse_dot_of(e, e2.out, e2.gate, nr_run, stored ? store_rs : vs);
+            const int r_epi = j < l - 1 ? mv_epi : last_epi;
+            e.ds(e2, nrhs, r_epi, CL_STENCIL, ds_bytes(r_epi, nr_run));
         }
         v.gate = g_run;
         // the MR step reads r_L and u_L (L = the steps the iteration
@@ -1472,7 +1494,8 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
         const int nbg = std::min(nbv, GRAM_NBMAX);
         e.gram(v, nrhs, nbg, CL_SEED, nr_run * (l + 1.0) * nd * cB);
         s.nblk = nbg;
-        e.scalar(OP_SC_MR, s, nrhs);
+        s.then_defer = deferred ? 1 : 0;
+        e.sc_mr(s, nullptr, nrhs);
         s.nblk = nbv;   // the stages below read the MR update's nbv partials
         v.partials = 1;
         // seed: read r_0..r_l, u_0..u_l, rt, write r_0, u_0; shift s: read
@@ -1486,7 +1509,6 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
             // every shift's update over the iteration, from the basis: read the
             // 2l+2 basis vectors once, each active shift's u^s_0 and x^s (FP64)
             // read and written
-            e.scalar(OP_SC_DEFER, s, nrhs);
             v.gate = g_run;
             e.defer_update(v, nrhs, nbv, CL_SHIFT_MR, nr_run * nb * nd * cB + nsh_act * (2.0 * cB + 32.0) * nd);
         }
@@ -1498,7 +1520,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
             else
                 reliable_update(e, v, g_rel, nullptr, CoefRef{}, nr_run);
         }
-        e.scalar(OP_SC_CONV, s, nrhs);
+        conv_stage(e, s);
     };
 
     CHK(ensure_host(c, (size_t)2 * nrhs * sizeof(SeedState)));   // two iterations' states
