@@ -829,8 +829,10 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
     // Blocks per right-hand side of the launches whose gates are nearly always
     // closed (the exhaustion test's norm, the completion of a step that ended
     // early): the 2048 of a streaming pass only to find the gate closed took
-    // 30 us for 12 right-hand sides
-    const int nbq = std::min(nbv, 256);
+    // 30 us for 12 right-hand sides.  4096 blocks per launch still stream at
+    // the memory's rate where the gate is open (one right-hand side on
+    // 24^3x48: 29 us, 47 with 256 blocks)
+    const int nbq = std::min(nbv, std::max(256, 4096 / nrhs));
     const long ps = part_stride(c->g);
     const size_t cs = sizeof(C<T>);
     const long vs = (long)(l + 1) * n;   // rhs stride of R and U
