@@ -85,6 +85,7 @@ __global__ __launch_bounds__(BLOCK) void k_defer_update(VecArgs<T> a) {
     constexpr int NB = 2 * L + 2;
     const long n = a.n;
     const int nact = a.seed[rhs].nact;
+    const bool first = a.seed[rhs].m == 0;   // u^s_0 = x^s = 0: written, not read
     const C<T> *B = a.Bm + (size_t)rhs * NB * n;
     const DeferCoef *dc = a.dc + (size_t)rhs * NSMAX;
     // one shift's update of element e from its loaded u^s_0 and x^s
@@ -120,8 +121,14 @@ __global__ __launch_bounds__(BLOCK) void k_defer_update(VecArgs<T> a) {
         for (; q + 1 < nact; q += 2) {
             const DeferCoef &d0 = dc[q], &d1 = dc[q + 1];
             const size_t o0 = ((size_t)rhs * a.nshift + d0.s) * n + e, o1 = ((size_t)rhs * a.nshift + d1.s) * n + e;
-            const C<T> u0 = a.W0[o0], u1 = a.W0[o1];
-            const double2 x0 = a.X[o0], x1 = a.X[o1];
+            C<T> u0 = mk<T>(0, 0), u1 = u0;
+            double2 x0 = d2(0, 0), x1 = x0;
+            if (!first) {
+                u0 = a.W0[o0];
+                u1 = a.W0[o1];
+                x0 = a.X[o0];
+                x1 = a.X[o1];
+            }
             if (d0.live) upd(d0, b, e, u0, x0);
             if (d1.live) upd(d1, b, e, u1, x1);
         }
@@ -129,7 +136,7 @@ __global__ __launch_bounds__(BLOCK) void k_defer_update(VecArgs<T> a) {
             const DeferCoef &d = dc[q];
             if (d.live) {
                 const size_t o = ((size_t)rhs * a.nshift + d.s) * n + e;
-                upd(d, b, e, a.W0[o], a.X[o]);
+                upd(d, b, e, first ? mk<T>(0, 0) : a.W0[o], first ? d2(0, 0) : a.X[o]);
             }
         }
     }
@@ -186,8 +193,9 @@ __global__ void k_convert_out(double2 *dst, const C<T> *src, long n, long ds, lo
 }
 
 template <typename T>
-__global__ void k_zero(C<T> *dst, long n, long stride) {
+__global__ void k_zero(C<T> *dst, long n, long stride, Gate gate) {
     const int rhs = blockIdx.y;
+    if (!gate_open(gate, rhs)) return;
     for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long)gridDim.x * blockDim.x)
         dst[rhs * stride + e] = mk<T>(0, 0);
 }
@@ -433,7 +441,10 @@ void launch_convert_out(hipStream_t st, double2 *dst, const C<T> *src, long n, l
 }
 template <typename T>
 void launch_zero(hipStream_t st, C<T> *dst, long n, long stride, int nrhs) {
-    hipLaunchKernelGGL((k_zero<T>), dim3(nblocks_for(n), nrhs), dim3(BLOCK), 0, st, dst, n, stride);
+    hipLaunchKernelGGL((k_zero<T>), dim3(nblocks_for(n), nrhs), dim3(BLOCK), 0, st, dst, n, stride, Gate{});
+}
+void launch_zero_gated(hipStream_t st, double2 *dst, long n, long stride, int nrhs, int nblk, Gate gate) {
+    hipLaunchKernelGGL((k_zero<double>), dim3(nblk, nrhs), dim3(BLOCK), 0, st, dst, n, stride, gate);
 }
 template <typename T>
 void launch_dot_partials(hipStream_t st, const C<T> *x, const C<T> *y, long n, double *part, long ps,

@@ -423,6 +423,7 @@ __device__ __forceinline__ void basis_mr_update_body(const BasisArgs<double> &a,
             if (f < 2) break;
         }
     const int nact = SHIFTS ? S.nact : 0;
+    const bool first = S.m == 0;   // u^s_0 = x^s = 0: written, not read
     const DeferCoef *dc = SHIFTS ? a.dc + (size_t)rhs * NSMAX : nullptr;
     const long n = a.n;
     double2 *R0 = a.R0 + (size_t)rhs * a.r0_rs, *U0 = a.U0 + (size_t)rhs * a.u0_rs;
@@ -473,14 +474,20 @@ __device__ __forceinline__ void basis_mr_update_body(const BasisArgs<double> &a,
             for (; q + 1 < nact; q += 2) {
                 const DeferCoef &d0 = dc[q], &d1 = dc[q + 1];
                 const size_t o0 = ((size_t)rhs * a.nshift + d0.s) * n + e, o1 = ((size_t)rhs * a.nshift + d1.s) * n + e;
-                const double2 w0 = a.W0[o0], w1 = a.W0[o1], x0 = a.X[o0], x1 = a.X[o1];
+                double2 w0 = d2(0, 0), w1 = w0, x0 = w0, x1 = w0;
+                if (!first) {
+                    w0 = a.W0[o0];
+                    w1 = a.W0[o1];
+                    x0 = a.X[o0];
+                    x1 = a.X[o1];
+                }
                 upd(d0, o0, w0, x0);
                 upd(d1, o1, w1, x1);
             }
             if (q < nact) {
                 const DeferCoef &d = dc[q];
                 const size_t o = ((size_t)rhs * a.nshift + d.s) * n + e;
-                upd(d, o, a.W0[o], a.X[o]);
+                upd(d, o, first ? d2(0, 0) : a.W0[o], first ? d2(0, 0) : a.X[o]);
             }
         }
     }

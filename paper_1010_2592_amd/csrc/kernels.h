@@ -290,6 +290,7 @@ void launch_convert_out(hipStream_t, double2 *dst, const C<T> *src, long n, long
                         long src_stride, int nrhs);
 template <typename T>
 void launch_zero(hipStream_t, C<T> *dst, long n, long stride, int nrhs);
+void launch_zero_gated(hipStream_t, double2 *dst, long n, long stride, int nrhs, int nblk, Gate gate);
 
 // sparse shadow residual: index list of the nonzero entries of v ([nrhs] rows
 // of n at stride rs), at most spmax per row, in index order.  Returns the

@@ -986,8 +986,8 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
 
     // ---- initial vectors: r_0 = b, everything else zero
     {
-        Prof p(c, CL_OTHER, nrhs * nd * cB * (2.0 * (l + 1) + (pass1 ? ns * (double)wslots : 0.0)) +
-                                (pass1 ? nrhs * nd * ns * 16.0 : 0.0) + (mixed ? nrhs * nd * 16.0 : 0.0) +
+        Prof p(c, CL_OTHER, nrhs * nd * cB * (2.0 * (l + 1) + (pass1 && !deferred ? ns * (double)wslots : 0.0)) +
+                                (pass1 && !deferred ? nrhs * nd * ns * 16.0 : 0.0) + (mixed ? nrhs * nd * 16.0 : 0.0) +
                                 nrhs * nd * (16.0 + cB) + nrhs * nd * cB);
         if (basis) {
             // the basis form reads rows 1..l of R and U only where a step of
@@ -997,7 +997,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
             launch_zero<T>(st, R, (long)nrhs * (l + 1) * n, 0, 1);
             launch_zero<T>(st, Uv, (long)nrhs * (l + 1) * n, 0, 1);
         }
-        if (pass1) {
+        if (pass1 && !deferred) {   // the first deferred update writes both without reading them
             launch_zero<T>(st, W, (long)nrhs * ns * wslots * n, 0, 1);
             launch_zero<double>(st, X, (long)nrhs * ns * n, 0, 1);
         }
@@ -1080,6 +1080,15 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
     {
         Prof p(c, CL_SCALAR, 0);
         launch_sc_init(st, sa, nrhs);
+    }
+    if (deferred) {
+        // the solutions of a source that does not iterate (zero)
+        Gate g;
+        g.flag = &seed[0].run;
+        g.flag_stride = (long)sizeof(SeedState) / (long)sizeof(int);
+        g.need = 0;
+        g.eq = 1;
+        launch_zero_gated(st, X, (long)ns * n, (long)ns * n, nrhs, nbq, g);
     }
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
