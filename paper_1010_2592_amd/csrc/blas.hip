@@ -33,9 +33,9 @@ namespace {
 
 using namespace dev;
 
-template <typename T, int J, int MODE>
+template <typename T, int J, bool ONE>
 __global__ __launch_bounds__(BLOCK) void k_seed_u(VecArgs<T> a) {
-    seed_u_body<T, J, MODE>(a, blockIdx.x, gridDim.x, blockIdx.y);
+    seed_u_body<T, J, ONE>(a, blockIdx.x, gridDim.x, blockIdx.y);
 }
 
 template <typename T, int J, bool SHIFTS, bool XH, bool FU>
@@ -325,22 +325,20 @@ __global__ __launch_bounds__(BLOCK) void k_basis_combine(BasisArgs<double> a) {
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-template <typename T, int MODE>
+template <typename T, bool ONE>
 static void seed_u_j(hipStream_t st, const VecArgs<T> &a, int j, dim3 g, dim3 b) {
     switch (j) {
-#define C_(J) case J: hipLaunchKernelGGL((k_seed_u<T, J, MODE>), g, b, 0, st, a); break;
+#define C_(J) case J: hipLaunchKernelGGL((k_seed_u<T, J, ONE>), g, b, 0, st, a); break;
         C_(0) C_(1) C_(2) C_(3) C_(4) C_(5) C_(6) C_(7)
 #undef C_
     }
 }
 
 template <typename T>
-void launch_seed_u(hipStream_t st, const VecArgs<T> &a, int j, int nrhs, int nblk, int mode) {
+void launch_seed_u(hipStream_t st, const VecArgs<T> &a, int j, int nrhs, int nblk, bool one) {
     dim3 g(nblk, nrhs), b(BLOCK);
-    if (mode == 1) seed_u_j<T, 1>(st, a, j, g, b);
-    else if (mode == 2) {
-        if (j >= 1) seed_u_j<T, 2>(st, a, j, g, b);
-    } else seed_u_j<T, 0>(st, a, j, g, b);
+    if (one) seed_u_j<T, true>(st, a, j, g, b);
+    else seed_u_j<T, false>(st, a, j, g, b);
 }
 
 template <typename T, bool SH, bool XH, bool FU>
@@ -596,7 +594,7 @@ void launch_sparse_dot(hipStream_t st, const SparseDotArgs &a, int nrhs) {
 }
 
 #define INST(T)                                                                                  \
-    template void launch_seed_u<T>(hipStream_t, const VecArgs<T> &, int, int, int, int);                \
+    template void launch_seed_u<T>(hipStream_t, const VecArgs<T> &, int, int, int, bool);               \
     template void launch_r_update<T>(hipStream_t, const VecArgs<T> &, int, bool, bool, int, int, bool); \
     template void launch_gram<T>(hipStream_t, const VecArgs<T> &, int, int);                     \
     template void launch_snapshot<T>(hipStream_t, const VecArgs<T> &, int, int);                 \

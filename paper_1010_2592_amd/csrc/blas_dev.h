@@ -61,15 +61,9 @@ __device__ __forceinline__ MRView<T> mr_view(const VecArgs<T> &a, int rhs, int l
 }
 
 // ---------------------------------------------------------------------------
-// u_i = r_i - beta u_i for i in [I0, I1]: MODE 0 all of 0..J (the BiCG step's
-// direction update), MODE 1 only u_J (the one the step's Mv needs; the others
-// then follow in the fused r-update), MODE 2 only u_0..u_{J-1} (completes a
-// step that ended after its Mv of u_J).
-template <typename T, int J, int MODE = 0>
-__device__ __forceinline__ void seed_u_body(const VecArgs<T> &a, int bx, int gx, int rhs) {
-    constexpr int I0 = (MODE == 1) ? J : 0;
-    constexpr int I1 = (MODE == 2) ? J - 1 : J;
-    if (!gate_open(a.gate, rhs)) return;
+// u_i = r_i - beta u_i for i in [I0, I1]
+template <typename T, int I0, int I1>
+__device__ __forceinline__ void seed_u_update(const VecArgs<T> &a, int bx, int gx, int rhs) {
     const long n = a.n;
     const C<T> beta = cvt<T>(ld(a.beta, rhs));
     C<T> *R = a.R + (size_t)rhs * (a.l + 1) * n;
@@ -83,14 +77,28 @@ __device__ __forceinline__ void seed_u_body(const VecArgs<T> &a, int bx, int gx,
         }
     }
 }
+// The BiCG step's direction update: ONE = false all of u_0..u_J, ONE = true
+// only u_J (the one the step's Mv needs; the others then follow in the fused
+// r-update).
+template <typename T, int J, bool ONE = false>
+__device__ __forceinline__ void seed_u_body(const VecArgs<T> &a, int bx, int gx, int rhs) {
+    if (gate_open(a.gate, rhs)) seed_u_update<T, ONE ? J : 0, J>(a, bx, gx, rhs);
+}
 
 // r_i -= alpha u_{i+1}, i = 0..J.  FU (fused): the step's direction update of
 // u_0..u_{J-1} (u_i = r_i - beta u_i, deferred from before the Mv, which
 // needs only u_J) is done here on the same pass, with the same arithmetic:
-// u_0..u_{J-1} are read once, updated in registers and written back.
+// u_0..u_{J-1} are read once, updated in registers and written back.  A step
+// that ended after its Mv of u_J (alpha breakdown) still owes u_0..u_{J-1}
+// that update, which the partial MR step reads: VecArgs::gate_u.  (A launch
+// of its own for it, its gate nearly always closed, took 2 to 11 us a step.)
 template <typename T, int J, bool SHIFTS, bool XH, bool FU = false>
 __device__ __forceinline__ void r_update_body(const VecArgs<T> &a, int bx, int gx, int rhs) {
-    if (!gate_open(a.gate, rhs)) return;
+    if (!gate_open(a.gate, rhs)) {
+        if constexpr (FU && J >= 1)
+            if (a.has_gate_u && gate_open(a.gate_u, rhs)) seed_u_update<T, 0, J - 1>(a, bx, gx, rhs);
+        return;
+    }
     const long n = a.n;
     const double2 alpha_d = ld(a.alpha, rhs);
     const C<T> alpha = cvt<T>(alpha_d);

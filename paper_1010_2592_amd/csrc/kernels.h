@@ -173,6 +173,10 @@ struct VecArgs {
     CoefRef gam;                // gamma_1 at gam, gamma_i at gam.p + (i-1)*16
     int partials = 1;
     Gate gate{};
+    // fused r-update whose own gate is closed: with this one open (its step
+    // ended after its u-Mv) it makes the step's direction update alone
+    Gate gate_u{};
+    int has_gate_u = 0;
     // deferred single pass
     C<T> *Bm = nullptr;         // [rhs][2l+2][n] the outer iteration's basis
     C<T> *W0 = nullptr;         // [rhs][nshift][n] u^s_0 of every shift
@@ -253,8 +257,8 @@ void launch_basis_gram(hipStream_t, const BasisArgs<double> &, int nrhs, int nbl
 // shifts: also every active shift's update over the outer iteration
 void launch_basis_mr_update(hipStream_t, const BasisArgs<double> &, bool shifts, int nrhs, int nblk);
 
-// mode: 0 u_0..u_j, 1 u_j only, 2 u_0..u_{j-1} (see seed_u_body)
-template <typename T> void launch_seed_u(hipStream_t, const VecArgs<T> &, int j, int nrhs, int nblk, int mode = 0);
+// one: u_j only (see seed_u_body)
+template <typename T> void launch_seed_u(hipStream_t, const VecArgs<T> &, int j, int nrhs, int nblk, bool one = false);
 // fused: the r-update also applies the step's deferred u_0..u_{j-1} update
 template <typename T>
 void launch_r_update(hipStream_t, const VecArgs<T> &, int j, bool shifts, bool xh, int nrhs, int nblk,

@@ -619,12 +619,12 @@ struct Emit {
             record(o, a);
         }
     }
-    // mode and fused (see launch_seed_u / launch_r_update) exist for the
+    // one and fused (see launch_seed_u / launch_r_update) exist for the
     // per-stage launches only; the persistent kernel runs the plain stages
-    void seed_u(const VecArgs<T> &a, int j, int nrhs, int nblk, int cls, double bytes, int umode = 0) {
+    void seed_u(const VecArgs<T> &a, int j, int nrhs, int nblk, int cls, double bytes, bool one = false) {
         if (launching(cls, bytes)) {
             Prof p(c, cls, bytes);
-            launch_seed_u<T>(st, a, j, nrhs, nblk, umode);
+            launch_seed_u<T>(st, a, j, nrhs, nblk, one);
         } else if (mode == RECORD) {
             POp o = op(OP_SEED_U, cls, nblk * nrhs);
             o.j = j;
@@ -827,11 +827,10 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
     const int nbd = (V + CHUNK - 1) / CHUNK;     // stencil partials: one per 64-site chunk
     const int nbv = nblocks_for(n);
     // Blocks per right-hand side of the launches whose gates are nearly always
-    // closed (the exhaustion test's norm, the completion of a step that ended
-    // early): the 2048 of a streaming pass only to find the gate closed took
-    // 30 us for 12 right-hand sides.  4096 blocks per launch still stream at
-    // the memory's rate where the gate is open (one right-hand side on
-    // 24^3x48: 29 us, 47 with 256 blocks)
+    // closed (the exhaustion test's norm): the 2048 of a streaming pass only
+    // to find the gate closed took 30 us for 12 right-hand sides.  4096 blocks
+    // per launch still stream at the memory's rate where the gate is open (one
+    // right-hand side on 24^3x48: 29 us, 47 with 256 blocks)
     const int nbq = std::min(nbv, std::max(256, 4096 / nrhs));
     const long ps = part_stride(c->g);
     const size_t cs = sizeof(C<T>);
@@ -1444,7 +1443,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
             from_store(v, j, j);     // r_j and u_j: this step's first update of both
             // fused form: only u_j before its Mv; u_0..u_{j-1} in the r-update
             const bool fu = fuse_seed && j >= 1;
-            e.seed_u(v, j, nrhs, nbv, CL_SEED, nr_run * (fu ? 3.0 : 3.0 * (j + 1)) * nd * cB, fu ? 1 : 0);
+            e.seed_u(v, j, nrhs, nbv, CL_SEED, nr_run * (fu ? 3.0 : 3.0 * (j + 1)) * nd * cB, fu);
             // u_{j+1} = S u_j = a g5 D (g5 D u_j) + sigma0 u_j, <rt, u_{j+1}>
             e1.in = Uv + (size_t)j * n;
             e1.out = tmp;
@@ -1461,6 +1460,13 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
             e.ds(e2, nrhs, mv_epi, CL_STENCIL, ds_bytes(mv_epi, nr_run));
             alpha_stage(e, s, e2.out, stored ? store_rs : vs, false);
             v.partials = 1;
+            // where the step ended after its u-Mv the fused update completes u_0..u_{j-1}
+            v.gate_u = g_run;
+            v.gate_u.flag = &seed[0].step_flag[j];
+            v.gate_u.flag_stride = (long)sizeof(SeedState) / (long)sizeof(int);
+            v.gate_u.need = 1;
+            v.gate_u.eq = 1;
+            v.has_gate_u = fu ? 1 : 0;
             from_store(v, j, j + 1);     // r_j (first update) and u_{j+1} (read only)
             // seed: read r_i, u_{i+1}, write r_i; shift s (per-step form): read
             // u^s_0..j, x^s (FP64), write u^s_0..j+1, x^s
@@ -1468,17 +1474,6 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                        nr_run * ((fu ? 4.0 * j + 4 : 3.0 * (j + 1)) * cB + (mixed ? 32.0 : 0.0)) * nd +
                            (shifts_step ? nsh_act * ((2.0 * j + 3) * cB + 32.0) * nd : 0.0),
                        fu);
-            if (fu) {
-                // a step that ended after its u-Mv (alpha breakdown) still
-                // owes u_0..u_{j-1} their update, which the partial MR step reads
-                VecArgs<T> vc = v;
-                vc.gate = g_run;
-                vc.gate.flag = &seed[0].step_flag[j];
-                vc.gate.flag_stride = (long)sizeof(SeedState) / (long)sizeof(int);
-                vc.gate.need = 1;
-                vc.gate.eq = 1;
-                e.seed_u(vc, j, nrhs, nbq, CL_SEED, 0.0, 2);
-            }
             // r_{j+1} = S r_j, <rt, r_{j+1}>
             e1.in = R + (size_t)j * n;
             if (!opw) e.ds(e1, nrhs, EPI_PLAIN, CL_STENCIL, ds_bytes(EPI_PLAIN, nr_run));
@@ -1864,7 +1859,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                 vb.alpha = CoefRef{(const char *)&drs[idx].alpha, rstride};
                 vb.gate = gu;
                 const bool fu = !P.persistent && j >= 1;
-                e.seed_u(vb, j, nrhs, nbv, CL_SEED, nr_m * (fu ? 3.0 : 3.0 * (j + 1)) * nd * cB, fu ? 1 : 0);
+                e.seed_u(vb, j, nrhs, nbv, CL_SEED, nr_m * (fu ? 3.0 : 3.0 * (j + 1)) * nd * cB, fu);
                 e1.in = Uv + (size_t)j * n;
                 e1.out = tmp;
                 e1.gate = gu;
@@ -1876,15 +1871,11 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                 e2.gate = gu;
                 e.ds(e2, nrhs, EPI_MV_Y, CL_STENCIL, ds_bytes(EPI_MV_Y, nr_m));
                 vb.gate = gr;
+                vb.gate_u = gu;      // the step ended after its u-Mv: u_0..u_{j-1} alone
+                vb.gate_u.eq = 1;
+                vb.has_gate_u = fu ? 1 : 0;
                 e.r_update(vb, j, false, mixed, nrhs, nbv, CL_SEED, nr_m * (fu ? 4.0 * j + 4 : 3.0 * (j + 1)) * nd * cB,
                            fu);
-                if (fu) {
-                    // the step ended after its u-Mv: complete u_0..u_{j-1}
-                    VecArgs<T> vc = vb;
-                    vc.gate = gu;
-                    vc.gate.eq = 1;
-                    e.seed_u(vc, j, nrhs, nbq, CL_SEED, 0.0, 2);
-                }
                 e1.in = R + (size_t)j * n;
                 e1.gate = gr;
                 if (!opw) e.ds(e1, nrhs, EPI_PLAIN, CL_STENCIL, ds_bytes(EPI_PLAIN, nr_m));
