@@ -84,33 +84,6 @@ __host__ __device__ inline bool cfinite(double2 a) { return isfinite(a.x) && isf
 
 template <typename T> __device__ inline C<T> to_c(double2 z) { return mk<T>((T)z.x, (T)z.y); }
 
-// ---------------------------------------------------------------------------
-// Deterministic block reduction (BLOCK = 256 threads = 4 wavefronts of 64).
-// Values are reduced by a fixed shuffle tree inside each wavefront, then the
-// four wavefront sums are added in order.  Thread k < NV writes value k to
-// out[k * stride].
-// ---------------------------------------------------------------------------
-template <int NV>
-__device__ inline void block_reduce_store(double (&v)[NV], double *out, int stride) {
-    __shared__ double sh[NV][BLOCK / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    __syncthreads();   // a block may call this back to back (persistent stages)
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-        double x = v[k];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
-        if (lane == 0) sh[k][wave] = x;
-    }
-    __syncthreads();
-    for (int k = threadIdx.x; k < NV; k += BLOCK) {
-        double s = sh[k][0];
-#pragma unroll
-        for (int w = 1; w < BLOCK / 64; ++w) s += sh[k][w];
-        out[(size_t)k * stride] = s;
-    }
-}
-
 // x + the value 32 (16) lanes away (H = 32: lane ^ 32, H = 16: lane ^ 16):
 // the swap instruction exchanges the upper half (odd rows) of one register
 // with the lower half (even rows) of the other, so with x in both the sum of
@@ -150,15 +123,115 @@ __device__ __forceinline__ double wave_sum(double x) {
     return ror_add<1>(x);
 }
 
-// Reduce NV doubles over the 64 lanes of a wavefront (the same data always
-// gives the same bits) and store them from lane 0 at out[k * stride].
+// One step of the sums of two values at once over lanes H apart: the lanes
+// without bit H get a's, the lanes with it b's.
+template <int H>
+__device__ __forceinline__ double pair_add(double a, double b) {
+    const int al = __double2loint(a), ah = __double2hiint(a), bl = __double2loint(b), bh = __double2hiint(b);
+    if constexpr (H == 32) {
+        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)al, (unsigned)bl, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)ah, (unsigned)bh, false, false);
+        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    } else if constexpr (H == 16) {
+        const auto l = __builtin_amdgcn_permlane16_swap((unsigned)al, (unsigned)bl, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap((unsigned)ah, (unsigned)bh, false, false);
+        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    } else {
+        // the other lane's value through DPP: a row rotation by 8 or row
+        // shifts by 4, each into the lanes of its bank mask, or quad permutes
+        const bool up = threadIdx.x & H;
+        int pl, ph;
+        if constexpr (H >= 4) {
+            constexpr int CA = H == 8 ? 0x128 : 0x104, CB = H == 8 ? 0x128 : 0x114;
+            constexpr int MA = H == 8 ? 0x3 : 0x5;
+            pl = __builtin_amdgcn_update_dpp(al, al, CA, 0xF, MA, false);
+            ph = __builtin_amdgcn_update_dpp(ah, ah, CA, 0xF, MA, false);
+            pl = __builtin_amdgcn_update_dpp(pl, bl, CB, 0xF, 0xF ^ MA, false);
+            ph = __builtin_amdgcn_update_dpp(ph, bh, CB, 0xF, 0xF ^ MA, false);
+        } else {
+            constexpr int Q = H == 2 ? 0x4E : 0xB1;   // lanes 2, 3, 0, 1 or 1, 0, 3, 2 of a quad
+            pl = __builtin_amdgcn_update_dpp(0, up ? al : bl, Q, 0xF, 0xF, false);
+            ph = __builtin_amdgcn_update_dpp(0, up ? ah : bh, Q, 0xF, 0xF, false);
+        }
+        return __hiloint2double(up ? bh : ah, up ? bl : al) + __hiloint2double(ph, pl);
+    }
+}
+// The sums of N values over the 64 lanes, N <= 2 * H, halving the number of
+// values at each step: 30 values take 33 steps instead of the 180 of a sum
+// each.  The lane whose number is k with its six bits reversed returns value
+// k's sum, in wave_sum's order.
+template <int N, int H = 32>
+__device__ __forceinline__ double wave_sums(const double (&v)[N]) {
+    if constexpr (H == 0) {
+        return v[0];
+    } else {
+        double w[(N + 1) / 2];
+#pragma unroll
+        for (int i = 0; i < (N + 1) / 2; ++i) w[i] = pair_add<H>(v[2 * i], v[2 * i + 1 < N ? 2 * i + 1 : 2 * i]);
+        return wave_sums<(N + 1) / 2, H / 2>(w);
+    }
+}
+// the number of the value whose sum wave_sums returns in this lane
+__device__ __forceinline__ int wave_sums_index() { return (int)(__brev(threadIdx.x & 63u) >> 26); }
+
+// How a wavefront's sums are formed: 1 halving the number of values at each
+// step, all VALU; 0 a shuffle tree per value, whose registers are fewer (the
+// persistent kernel sets 0 before including this header: its register budget
+// is the maximum over all its stages, and the other form took its FP64
+// instances from two wavefronts per SIMD to one).  The sums are the same bits.
+#ifndef MSB_WAVE_SUMS
+#define MSB_WAVE_SUMS 1
+#endif
+
+// Reduce NV <= 64 doubles over the 64 lanes of a wavefront (the same data
+// always gives the same bits) and store value k at out[k * stride].
 template <int NV>
 __device__ inline void wave_reduce_store(const double (&v)[NV], double *out, long stride) {
+#if MSB_WAVE_SUMS
+    const double x = wave_sums<NV>(v);
+    const int k = wave_sums_index();
+    if (k < NV) out[(size_t)k * stride] = x;
+#else
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-        const double x = wave_sum(v[k]);
+        double x = v[k];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
         if (lane == 0) out[(size_t)k * stride] = x;
+    }
+#endif
+}
+
+// ---------------------------------------------------------------------------
+// Deterministic block reduction (BLOCK = 256 threads = 4 wavefronts of 64).
+// Values are reduced by a fixed tree inside each wavefront, then the four
+// wavefront sums are added in order.  Thread k < NV writes value k to
+// out[k * stride].  The Gram kernels end in 30 sums (l = 4) per block after
+// one to a few elements per lane: as shuffle trees, 360 LDS operations per
+// wavefront, they were most of the kernel (FP32, 12 right-hand sides on
+// 10x9x7x14: 57 us, now 14).
+// ---------------------------------------------------------------------------
+template <int NV>
+__device__ inline void block_reduce_store(double (&v)[NV], double *out, int stride) {
+    __shared__ double sh[NV][BLOCK / 64];
+    const int wave = threadIdx.x >> 6;
+    __syncthreads();   // a block may call this back to back (persistent stages)
+    if constexpr (NV <= 64) {
+        wave_reduce_store<NV>(v, &sh[0][wave], BLOCK / 64);
+    } else {
+        double lo[64], hi[NV - 64];
+#pragma unroll
+        for (int k = 0; k < NV; ++k) (k < 64 ? lo[k < 64 ? k : 0] : hi[k < 64 ? 0 : k - 64]) = v[k];
+        wave_reduce_store<64>(lo, &sh[0][wave], BLOCK / 64);
+        wave_reduce_store<NV - 64>(hi, &sh[64][wave], BLOCK / 64);
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < NV; k += BLOCK) {
+        double s = sh[k][0];
+#pragma unroll
+        for (int w = 1; w < BLOCK / 64; ++w) s += sh[k][w];
+        out[(size_t)k * stride] = s;
     }
 }
 
@@ -232,17 +305,9 @@ __device__ inline void block_sum_rows(const double *p, long stride, const int *r
 #pragma unroll
             for (int u = 0; u < U; ++u) x[r] += v[r][u];
     }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x[r] += __shfl_down(x[r], off, 64);
-    }
+    const int wave = threadIdx.x >> 6;
     __syncthreads();
-    if (lane == 0) {
-#pragma unroll
-        for (int r = 0; r < NR; ++r) sh[r][wave] = x[r];
-    }
+    wave_reduce_store<NR>(x, &sh[0][wave], BLOCK / 64);
     __syncthreads();
     if (threadIdx.x < NR) {
         const int r = threadIdx.x;

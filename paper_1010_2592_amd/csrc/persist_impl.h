@@ -28,6 +28,7 @@
 // one load per partial in flight in the block sums: this kernel's register
 // budget is the maximum over all its stages (the sums are the same bits)
 #define MSB_SUM_PREFETCH 1
+#define MSB_WAVE_SUMS 0
 #include "barrier_tree.h"
 #include "blas_dev.h"
 #include "scalar_dev.h"

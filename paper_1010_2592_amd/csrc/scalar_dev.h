@@ -372,30 +372,45 @@ __device__ __forceinline__ void sc_mr_body(const ScalarArgs &a, int rhs) {
             }
         }
     } else {
-        // every pair at once: a wavefront per piece of a row (at most 44 pairs)
-        constexpr int NPX = (LMAX + 1) * (LMAX + 2) / 2;
+        // every pair at once: a wavefront per piece of a row (at most 44
+        // pairs), the loads of TB pieces in flight together (one piece at a
+        // time was a chain of trips to memory: 35 us at l = 6 on 24^3x48, now
+        // 28, the rest the serial factorisation)
+        constexpr int NPX = (LMAX + 1) * (LMAX + 2) / 2, NW = NT / 64, TB = 4, UP = 8;
+        static_assert(NW % 4 == 0, "a wavefront's pieces are the same quarter of their rows");
         __shared__ double sh[2 * NPX][4];
         const int lane = threadIdx.x & 63, np = (L + 1) * (L + 2) / 2;
-        for (int task = threadIdx.x >> 6; task < 8 * np; task += NT / 64) {
-            // pair number -> (i, k) over 0..L, its row in the kernel's numbering over 0..l
-            int i = 0, q = task >> 3;
-            while (q > L - i) {
-                q -= L + 1 - i;
-                ++i;
-            }
-            if (i == 0 && q == 0) continue;   // ||r_0||^2 is not part of the system
-            const double *pr = row + (size_t)(2 * pidx(i, i + q) + ((task >> 2) & 1)) * a.ps;
-            double x = 0.0;
-            constexpr int UP = 4;
-            for (int e = (task & 3) * 64 + lane; e < a.nblk; e += UP * BLOCK) {
-                double v[UP];
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        // pieces 0 .. 7 are ||r_0||^2, which is not part of the system
+        for (int t0 = 8 + wave; t0 < 8 * np; t0 += TB * NW) {
+            const double *pr[TB];
+            double x[TB];
 #pragma unroll
-                for (int u = 0; u < UP; ++u) v[u] = e + u * BLOCK < a.nblk ? pr[e + u * BLOCK] : 0.0;
-#pragma unroll
-                for (int u = 0; u < UP; ++u) x += v[u];
+            for (int b = 0; b < TB; ++b) {
+                // pair number -> (i, k) over 0..L, its row in the kernel's numbering over 0..l
+                const int task = t0 + b * NW < 8 * np ? t0 + b * NW : t0;
+                int i = 0, q = task >> 3;
+                while (q > L - i) {
+                    q -= L + 1 - i;
+                    ++i;
+                }
+                pr[b] = row + (size_t)(2 * pidx(i, i + q) + ((task >> 2) & 1)) * a.ps;
+                x[b] = 0.0;
             }
-            x = wave_sum(x);
-            if (lane == 0) sh[task >> 2][task & 3] = x;
+            for (int e = (t0 & 3) * 64 + lane; e < a.nblk; e += UP * BLOCK) {
+                double v[TB][UP];
+#pragma unroll
+                for (int b = 0; b < TB; ++b)
+#pragma unroll
+                    for (int u = 0; u < UP; ++u) v[b][u] = e + u * BLOCK < a.nblk ? pr[b][e + u * BLOCK] : 0.0;
+#pragma unroll
+                for (int b = 0; b < TB; ++b)
+#pragma unroll
+                    for (int u = 0; u < UP; ++u) x[b] += v[b][u];
+            }
+            const double s = wave_sums<TB>(x);
+            const int b = wave_sums_index(), task = t0 + b * NW;
+            if (b < TB && task < 8 * np) sh[task >> 2][task & 3] = s;
         }
         __syncthreads();
         if ((int)threadIdx.x < np) {
