@@ -66,17 +66,14 @@ __host__ __device__ inline double cabsd(double2 a) { return sqrt(a.x * a.x + a.y
 // psi range far beyond 1e+-154)
 __host__ __device__ inline double cmod(double2 a) { return hypot(a.x, a.y); }
 __host__ __device__ inline double2 cdiv(double2 a, double2 b) {
-    // Smith's algorithm: scale by the larger component of b
+    // Smith's algorithm: scale by the larger component of b, which is
+    // selected without a branch so that independent quotients overlap
+    const bool big = fabs(b.x) >= fabs(b.y);
+    const double u = big ? b.x : b.y, v = big ? b.y : b.x;
+    const double t = v / u, d = u + v * t;
     double2 r;
-    if (fabs(b.x) >= fabs(b.y)) {
-        double t = b.y / b.x, d = b.x + b.y * t;
-        r.x = (a.x + a.y * t) / d;
-        r.y = (a.y - a.x * t) / d;
-    } else {
-        double t = b.x / b.y, d = b.x * t + b.y;
-        r.x = (a.x * t + a.y) / d;
-        r.y = (a.y * t - a.x) / d;
-    }
+    r.x = ((big ? a.x : a.y) + (big ? a.y : a.x) * t) / d;
+    r.y = ((big ? a.y : -a.x) + (big ? -a.x : a.y) * t) / d;
     return r;
 }
 __host__ __device__ inline double2 d2(double re, double im) { double2 z; z.x = re; z.y = im; return z; }
@@ -209,7 +206,7 @@ __device__ inline void wave_reduce_store(const double (&v)[NV], double *out, lon
 // wavefront sums are added in order.  Thread k < NV writes value k to
 // out[k * stride].  The Gram kernels end in 30 sums (l = 4) per block after
 // one to a few elements per lane: as shuffle trees, 360 LDS operations per
-// wavefront, they were most of the kernel (FP32, 12 right-hand sides on
+// wavefront, they were most of the kernel (FP32, 6 right-hand sides on
 // 10x9x7x14: 57 us, now 14).
 // ---------------------------------------------------------------------------
 template <int NV>

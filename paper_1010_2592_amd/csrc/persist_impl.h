@@ -145,11 +145,26 @@ __device__ __forceinline__ bool grid_barrier(PersistCtl *ctl, unsigned long long
 // The scalar stages run in one block per right-hand side and are latency
 // bound; as separate functions their registers do not enter the allocation of
 // the stencil and vector stages inlined into the kernel.
-__device__ __noinline__ void call_sc_beta(const ScalarArgs *a, int rhs) { sc_beta_body(*a, rhs); }
-__device__ __noinline__ void call_sc_alpha(const ScalarArgs *a, int rhs) { sc_alpha_body(*a, rhs); }
-__device__ __noinline__ void call_sc_mr(const ScalarArgs *a, int rhs) { sc_mr_body(*a, rhs); }
-__device__ __noinline__ void call_sc_rel(const ScalarArgs *a, int rhs) { sc_rel_body(*a, rhs); }
-__device__ __noinline__ void call_sc_conv(const ScalarArgs *a, int rhs) { sc_conv_body(*a, rhs); }
+__device__ __noinline__ void call_sc_beta(const ScalarArgs *a, int rhs) {
+    StageState<BLOCK> st(*a, rhs);
+    sc_beta_body(*a, rhs, st);
+}
+__device__ __noinline__ void call_sc_alpha(const ScalarArgs *a, int rhs) {
+    StageState<BLOCK> st(*a, rhs);
+    sc_alpha_body(*a, rhs, st);
+}
+__device__ __noinline__ void call_sc_mr(const ScalarArgs *a, int rhs) {
+    StageState<BLOCK> st(*a, rhs);
+    sc_mr_body<0>(*a, rhs, st);
+}
+__device__ __noinline__ void call_sc_rel(const ScalarArgs *a, int rhs) {
+    StageState<BLOCK> st(*a, rhs);
+    sc_rel_body(*a, rhs, st);
+}
+__device__ __noinline__ void call_sc_conv(const ScalarArgs *a, int rhs) {
+    StageState<BLOCK> st(*a, rhs);
+    sc_conv_body(*a, rhs, st);
+}
 // The stencil of this kernel, one lane per site with the links read from
 // global memory, one hop at a time (two gather buffers would cost the kernel
 // an occupancy step): the same arithmetic and per-wavefront partials as the

@@ -29,26 +29,53 @@ namespace {
 using namespace dev;
 
 __global__ __launch_bounds__(BLOCK) void sc_init(ScalarArgs a) { sc_init_body(a, blockIdx.x); }
-__global__ __launch_bounds__(SC_THREADS) void sc_beta(ScalarArgs a) { sc_beta_body<SC_THREADS>(a, blockIdx.x); }
+__global__ __launch_bounds__(SC_THREADS) void sc_beta(ScalarArgs a) {
+    __shared__ StateLds l;
+    StageState<SC_THREADS> st(a, blockIdx.x, l);
+    sc_beta_body(a, blockIdx.x, st);
+    st.leave();
+}
 __global__ __launch_bounds__(SC_THREADS) void sc_alpha(ScalarArgs a) {
-    sc_alpha_body<SC_THREADS>(a, blockIdx.x);
-    if (!a.then_basis) return;
-    __syncthreads();   // the steps' flags and coefficients, written by one work-item
-    sc_basis_body(a, blockIdx.x);
+    __shared__ StateLds l;
+    StageState<SC_THREADS> st(a, blockIdx.x, l);
+    sc_alpha_body(a, blockIdx.x, st);
+    if (a.then_basis) {
+        __syncthreads();   // the steps' flags and coefficients, written by one work-item
+        sc_basis_body(a, blockIdx.x, st.S);
+    }
+    st.leave();
 }
 // The MR stage and what follows from its coefficients alone (512 work-items:
 // the deferred coefficients keep three columns of L + 1 in registers)
 constexpr int MR_THREADS = 512;
 template <int L>
 __global__ __launch_bounds__(MR_THREADS) void sc_mr(ScalarArgs a, BasisArgs<double> b) {
-    sc_mr_body<MR_THREADS>(a, blockIdx.x);
+    __shared__ StateLds l;
+    StageState<MR_THREADS> st(a, blockIdx.x, l);
+    sc_mr_body<L>(a, blockIdx.x, st);
     __syncthreads();
-    if (b.sp_cnt) basis_spec_body<L>(b, blockIdx.x);
-    if (a.then_defer) sc_defer_body<L>(a, blockIdx.x);
+    if (b.sp_cnt) basis_spec_body<L>(b, blockIdx.x, st.S);
+    if (a.then_defer) sc_defer_body<L>(a, blockIdx.x, st.S);
+    st.leave();
 }
-__global__ __launch_bounds__(SC_THREADS) void sc_rel(ScalarArgs a) { sc_rel_body<SC_THREADS>(a, blockIdx.x); }
-__global__ __launch_bounds__(SC_THREADS) void sc_conv(ScalarArgs a) { sc_conv_body<SC_THREADS>(a, blockIdx.x); }
-__global__ __launch_bounds__(SC_THREADS) void sc_exh(ScalarArgs a) { sc_exh_body<SC_THREADS>(a, blockIdx.x); }
+__global__ __launch_bounds__(SC_THREADS) void sc_rel(ScalarArgs a) {
+    __shared__ StateLds l;
+    StageState<SC_THREADS> st(a, blockIdx.x, l);
+    sc_rel_body(a, blockIdx.x, st);
+    st.leave();
+}
+__global__ __launch_bounds__(SC_THREADS) void sc_conv(ScalarArgs a) {
+    __shared__ StateLds l;
+    StageState<SC_THREADS> st(a, blockIdx.x, l);
+    sc_conv_body(a, blockIdx.x, st);
+    st.leave();
+}
+__global__ __launch_bounds__(SC_THREADS) void sc_exh(ScalarArgs a) {
+    __shared__ StateLds l;
+    StageState<SC_THREADS> st(a, blockIdx.x, l);
+    sc_exh_body(a, blockIdx.x, st);
+    st.leave();
+}
 __global__ __launch_bounds__(64) void sc_basis_replay(BasisReplayArgs a) { sc_basis_replay_body(a, blockIdx.x); }
 
 }  // namespace

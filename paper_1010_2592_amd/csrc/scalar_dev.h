@@ -10,13 +10,6 @@
 namespace msb {
 namespace dev {
 
-__device__ inline double2 cpowi_neg(double sp, int i) {
-    // (-sp)^i for integer i >= 0
-    double p = 1.0;
-    for (int k = 0; k < i; ++k) p *= -sp;
-    return d2(p, 0.0);
-}
-
 __device__ inline const double *prow(const ScalarArgs &a, int rhs) {
     return a.part + (size_t)rhs * PMAX * a.ps;
 }
@@ -25,6 +18,68 @@ __device__ inline const double *prow(const ScalarArgs &a, int rhs) {
 // dependent trips to memory in one block per right-hand side; sixteen
 // wavefronts take the rows of partial sums side by side.
 constexpr int SC_THREADS = 1024;
+
+// The state of one right-hand side as a scalar stage works on it.  The
+// one-launch stages (NT > BLOCK) hold it in LDS: every word is loaded by a
+// work-item of its own at the start, beside the partials and before any gate
+// is known, and stored back at the end (leave) if the stage's gate was open.
+// Read field by field, each dependent read (gate, list of active shifts,
+// shift) was a trip to memory of its own, since another XCD wrote it (with the
+// MR stage's factor in registers: 8^4 at l = 4, MR 15.5 us, now 13.5, alpha
+// 5.1, now 4.8; the overlap on 12^3x24 33.1 ms, now 32.3).
+// The persistent kernel (NT == BLOCK) works on the state in place.
+struct StateLds {
+    SeedState s;
+    ShiftState h[NSMAX];
+};
+template <int NT>
+struct StageState {
+    typedef unsigned long long __attribute__((may_alias)) Word;
+    static constexpr int WS = sizeof(SeedState) / 8, W = sizeof(StateLds) / 8, PER = (W + NT - 1) / NT;
+    static_assert(sizeof(SeedState) % 16 == 0 && sizeof(StateLds) == sizeof(SeedState) + NSMAX * sizeof(ShiftState),
+                  "the two arrays' words follow each other");
+    SeedState &S;
+    ShiftState *H;
+    Word *seed, *shifts;   // in memory
+    Word v[PER];
+    __device__ __forceinline__ StageState(const ScalarArgs &a, int rhs, StateLds &l)
+        : S(l.s), H(l.h), seed(reinterpret_cast<Word *>(a.seed + rhs)),
+          shifts(reinterpret_cast<Word *>(a.sh + (size_t)rhs * NSMAX)) {
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+            const int w = threadIdx.x + p * NT;
+            if (w < W) v[p] = w < WS ? seed[w] : shifts[w - WS];
+        }
+    }
+    // the state is in LDS for every work-item
+    __device__ __forceinline__ void arrive() {
+        Word *d = reinterpret_cast<Word *>(&S);
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+            const int w = threadIdx.x + p * NT;
+            if (w < W) d[w] = v[p];
+        }
+        __syncthreads();
+    }
+    // after the last write to it (every work-item calls it)
+    __device__ __forceinline__ void leave() {
+        __syncthreads();
+        const Word *d = reinterpret_cast<const Word *>(&S);
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+            const int w = threadIdx.x + p * NT;
+            if (w < W) (w < WS ? seed[w] : shifts[w - WS]) = d[w];
+        }
+    }
+};
+template <>
+struct StageState<BLOCK> {
+    SeedState &S;
+    ShiftState *H;
+    __device__ __forceinline__ StageState(const ScalarArgs &a, int rhs)
+        : S(a.seed[rhs]), H(a.sh + (size_t)rhs * NSMAX) {}
+    __device__ __forceinline__ void arrive() {}
+};
 
 // sums of rows rows[0 .. cnt) of the partials, as block_sum gives each
 template <int NT, int NR>
@@ -58,12 +113,12 @@ __device__ inline void sum3(const double *row, long ps, int n, double &s0, doubl
 // min over the active shifts of |zeta psi| (1e308 without any), for wavefront
 // 0: a shift per lane (NSMAX = 64 of them), since one lane's walk over the
 // shifts' states was a chain of trips to memory
-__device__ inline double min_shift_scale(const ScalarArgs &a, const SeedState &S, int rhs) {
+__device__ inline double min_shift_scale(const SeedState &S, const ShiftState *Hs) {
     static_assert(NSMAX == 64, "one shift per lane");
     double mn = 1e308;
     const int q = threadIdx.x & 63;
     if (q < S.nact) {
-        const ShiftState &H = a.sh[(size_t)rhs * NSMAX + S.act[q]];
+        const ShiftState &H = Hs[S.act[q]];
         if (H.active) {
             const double sc = cmod(cmul(H.zeta, H.psi));
             mn = sc < mn ? sc : mn;
@@ -127,17 +182,28 @@ __device__ __forceinline__ void sc_init_body(const ScalarArgs &a, int rhs) {
 }
 
 // <r~, x> from the list of r~'s nonzero entries, each product formed in FP64
-// as the dense epilogues do (every work-item walks the list: at most
-// SPARSE_MAX entries)
+// as the dense epilogues do.  A lane of wavefront 0 per entry loads it and x
+// there (its entry before the count is known), then every work-item adds the
+// products in the list's order.
 template <typename X>
 __device__ inline double2 sparse_sum(const SparseVec &v, int rhs) {
+    __shared__ double2 ts[SPARSE_MAX], zs[SPARSE_MAX];
+    const int nk = v.cnt[rhs], k0 = threadIdx.x;
+    if (k0 < v.spmax && k0 < SPARSE_MAX) {
+        const double2 t = v.val[(size_t)rhs * v.spmax + k0];
+        const auto e = v.idx[(size_t)rhs * v.spmax + k0];
+        if (k0 < nk) {
+            const X z = reinterpret_cast<const X *>(v.x)[(size_t)rhs * v.x_rs + e];
+            ts[k0] = t;
+            zs[k0] = d2((double)z.x, (double)z.y);
+        }
+    }
+    __syncthreads();
     double p0 = 0.0, p1 = 0.0;
-    const int nk = v.cnt[rhs];
     for (int k = 0; k < nk; ++k) {
-        const double2 t = v.val[(size_t)rhs * v.spmax + k];
-        const X z = reinterpret_cast<const X *>(v.x)[(size_t)rhs * v.x_rs + v.idx[(size_t)rhs * v.spmax + k]];
-        p0 += t.x * (double)z.x + t.y * (double)z.y;
-        p1 += t.x * (double)z.y - t.y * (double)z.x;
+        const double2 t = ts[k], z = zs[k];
+        p0 += t.x * z.x + t.y * z.y;
+        p1 += t.x * z.y - t.y * z.x;
     }
     return d2(p0, p1);
 }
@@ -189,22 +255,26 @@ __device__ __forceinline__ void beta_step(const ScalarArgs &a, SeedState &S, int
     }
 }
 
-template <int NT = BLOCK>
-__device__ __forceinline__ void sc_beta_body(const ScalarArgs &a, int rhs) {
-    SeedState &S = a.seed[rhs];
-    if (!S.run || !S.bicg_on) return;
+template <int NT>
+__device__ __forceinline__ void sc_beta_body(const ScalarArgs &a, int rhs, StageState<NT> &st) {
+    SeedState &S = st.S;
+    if (NT == BLOCK && (!S.run || !S.bicg_on)) return;
     const int j = a.j;
     const double *row = prow(a, rhs);
+    double re, im, rj2, r02 = 0.0;
+    dot_sums<NT>(a, rhs, re, im, rj2);
     // basis form: ||r_0|| exists only where sc_exh found that the test could
     // fire; elsewhere it cannot (||r_0|| >= ||r_{j-1}|| / ||S||^(j-1))
+    if (NT != BLOCK) {
+        if (j >= 1 && !a.basis) r02 = sum1<NT>(row + 3 * a.ps, a.nblk2);
+        st.arrive();
+        if (!S.run || !S.bicg_on) return;
+    }
     const bool have_r0 = !a.basis || S.exh_check;
     const bool test = j >= 1 && have_r0 && !S.forced && S.nact > 0;
-    double re, im, rj2;
-    dot_sums<NT>(a, rhs, re, im, rj2);
-    double r02 = 0.0;
-    if (j >= 1 && have_r0) r02 = sum1<NT>(row + 3 * a.ps, a.nblk2);
+    if (j >= 1 && have_r0 && (NT == BLOCK || a.basis)) r02 = sum1<NT>(row + 3 * a.ps, a.nblk2);
     if (threadIdx.x >= 64) return;
-    const double mn = test ? min_shift_scale(a, S, rhs) : 0.0;
+    const double mn = test ? min_shift_scale(S, st.H) : 0.0;
     if (threadIdx.x != 0) return;
     if (j >= 1 && have_r0) S.rnorm0 = sqrt(r02);
     if (test) {
@@ -220,13 +290,15 @@ __device__ __forceinline__ void sc_beta_body(const ScalarArgs &a, int rhs) {
     beta_step(a, S, rhs, j, d2(re, im), rj2);
 }
 
-template <int NT = BLOCK>
-__device__ __forceinline__ void sc_alpha_body(const ScalarArgs &a, int rhs) {
-    SeedState &S = a.seed[rhs];
-    if (!S.run || !S.bicg_on) return;
+template <int NT>
+__device__ __forceinline__ void sc_alpha_body(const ScalarArgs &a, int rhs, StageState<NT> &st) {
+    SeedState &S = st.S;
+    if (NT == BLOCK && (!S.run || !S.bicg_on)) return;
     const int j = a.j;
     double re, im, u2;
     dot_sums<NT>(a, rhs, re, im, u2);
+    st.arrive();
+    if (NT != BLOCK && (!S.run || !S.bicg_on)) return;
     __shared__ int ok;
     __shared__ double2 sh_alpha, sh_beta;
     if (threadIdx.x == 0) {
@@ -262,7 +334,7 @@ __device__ __forceinline__ void sc_alpha_body(const ScalarArgs &a, int rhs) {
     const int nact = S.nact;
     for (int q = threadIdx.x; q < nact; q += BLOCK) {
         const int s = S.act[q];
-        ShiftState &H = a.sh[(size_t)rhs * NSMAX + s];
+        ShiftState &H = st.H[s];
         StepCoef &c = a.sc[(size_t)rhs * NSMAX + q];
         c.s = s;
         if (!H.active) {
@@ -316,12 +388,36 @@ __device__ __forceinline__ void sc_alpha_body(const ScalarArgs &a, int rhs) {
     }
 }
 
-template <int NT = BLOCK>
-__device__ __forceinline__ void sc_mr_body(const ScalarArgs &a, int rhs) {
-    SeedState &S = a.seed[rhs];
-    if (!S.run) return;
+// The factorisation has two forms, registers and LDS, that have to give the
+// same bits.  rounded: x, which the compiler may not fuse with what it goes
+// into (a product into a difference, a root into a reciprocal root).  Then
+// acc - a conj(b), acc - a b and acc - conj(a) b with the product fused as the
+// compiler does in the LDS form, whose loops leave it no other choice.
+__device__ inline double rounded(double x) {
+    asm("" : "+v"(x));
+    return x;
+}
+__device__ inline double2 rounded(double2 x) { return d2(rounded(x.x), rounded(x.y)); }
+__device__ inline double2 sub_mulc(double2 acc, double2 a, double2 b) {
+    return d2(acc.x - __builtin_fma(a.x, b.x, a.y * b.y), acc.y - __builtin_fma(a.y, b.x, -(a.x * b.y)));
+}
+__device__ inline double2 sub_mul(double2 acc, double2 a, double2 b) {
+    return d2(acc.x - __builtin_fma(a.x, b.x, -(a.y * b.y)), acc.y - __builtin_fma(a.y, b.x, a.x * b.y));
+}
+__device__ inline double2 sub_cmul(double2 acc, double2 a, double2 b) {
+    return d2(acc.x - __builtin_fma(a.x, b.x, a.y * b.y), acc.y - __builtin_fma(a.x, b.y, -(a.y * b.x)));
+}
+
+// LT: the compile-time l of a one-launch stage, 0 in the persistent kernel
+template <int LT, int NT>
+__device__ __forceinline__ void sc_mr_body(const ScalarArgs &a, int rhs, StageState<NT> &st) {
+    SeedState &S = st.S;
+    if (NT == BLOCK && !S.run) return;
     const int l = a.l;
-    const int L = S.exhausted ? 0 : S.l_eff;
+    // terms to sum: those of the steps taken, or all l where the sums are
+    // formed before the state has arrived (the others are not used)
+    int L = l;
+    if (NT == BLOCK) L = S.exhausted ? 0 : S.l_eff;
     __shared__ double2 G[LMAX][LMAX];
     __shared__ double2 cvec[LMAX];
     __shared__ double2 g[LMAX];
@@ -412,7 +508,8 @@ __device__ __forceinline__ void sc_mr_body(const ScalarArgs &a, int rhs) {
             const int b = wave_sums_index(), task = t0 + b * NW;
             if (b < TB && task < 8 * np) sh[task >> 2][task & 3] = s;
         }
-        __syncthreads();
+        st.arrive();
+        if (!S.run) return;
         if ((int)threadIdx.x < np) {
             int i = 0, q = threadIdx.x;
             while (q > L - i) {
@@ -431,40 +528,89 @@ __device__ __forceinline__ void sc_mr_body(const ScalarArgs &a, int rhs) {
                 }
             }
         }
+        L = S.exhausted ? 0 : S.l_eff;
         __syncthreads();
     }
     if (threadIdx.x == 0) {
         int n = L;
         int kok = n;
-        if (n > 0) {
+        if constexpr (LT > 0) {
+            // the factor in registers, every loop unrolled: through LDS each
+            // operand was a dependent trip (rows from n on are formed where
+            // that needs no branch, and not used)
             double dmax = 0.0;
             for (int i = 0; i < n; ++i) dmax = G[i][i].x > dmax ? G[i][i].x : dmax;
-            for (int i = 0; i < n; ++i) {
+            double2 F[LT][LT], z[LT], x[LT];
+            double inv[LT];
+#pragma unroll
+            for (int i = 0; i < LT; ++i) {
+                if (i >= kok) continue;
                 double d = G[i][i].x;
-                for (int p = 0; p < i; ++p) d -= cabs2(Lm[i][p]);
+#pragma unroll
+                for (int p = 0; p < i; ++p) d -= __builtin_fma(F[i][p].x, F[i][p].x, F[i][p].y * F[i][p].y);
                 if (!(d > CHOL_REL * dmax)) {
                     kok = i;
-                    break;
+                    continue;
                 }
-                const double dd = sqrt(d);
-                Lm[i][i] = d2(dd, 0.0);
-                for (int r = i + 1; r < n; ++r) {
+                inv[i] = 1.0 / rounded(sqrt(d));
+#pragma unroll
+                for (int r = i + 1; r < LT; ++r) {
                     double2 acc = G[r][i];
-                    for (int p = 0; p < i; ++p) acc = csub(acc, cmul(Lm[r][p], cconj(Lm[i][p])));
-                    Lm[r][i] = cscale(acc, 1.0 / dd);
+#pragma unroll
+                    for (int p = 0; p < i; ++p) acc = sub_mulc(acc, F[r][p], F[i][p]);
+                    F[r][i] = rounded(cscale(acc, inv[i]));
                 }
             }
-        }
-        n = kok;
-        for (int i = 0; i < n; ++i) {
-            double2 acc = cvec[i];
-            for (int p = 0; p < i; ++p) acc = csub(acc, cmul(Lm[i][p], zz[p]));
-            zz[i] = cscale(acc, 1.0 / Lm[i][i].x);
-        }
-        for (int i = n - 1; i >= 0; --i) {
-            double2 acc = zz[i];
-            for (int p = i + 1; p < n; ++p) acc = csub(acc, cmul(cconj(Lm[p][i]), g[p]));
-            g[i] = cscale(acc, 1.0 / Lm[i][i].x);
+            n = kok;
+#pragma unroll
+            for (int i = 0; i < LT; ++i) {
+                if (i >= n) continue;
+                double2 acc = cvec[i];
+#pragma unroll
+                for (int p = 0; p < i; ++p) acc = sub_mul(acc, F[i][p], z[p]);
+                z[i] = rounded(cscale(acc, inv[i]));
+            }
+#pragma unroll
+            for (int i = LT - 1; i >= 0; --i) {
+                if (i >= n) continue;
+                double2 acc = z[i];
+#pragma unroll
+                for (int p = i + 1; p < LT; ++p)
+                    if (p < n) acc = sub_cmul(acc, F[p][i], x[p]);
+                x[i] = rounded(cscale(acc, inv[i]));
+                g[i] = x[i];
+            }
+        } else {
+            if (n > 0) {
+                double dmax = 0.0;
+                for (int i = 0; i < n; ++i) dmax = G[i][i].x > dmax ? G[i][i].x : dmax;
+                for (int i = 0; i < n; ++i) {
+                    double d = G[i][i].x;
+                    for (int p = 0; p < i; ++p) d -= cabs2(Lm[i][p]);
+                    if (!(d > CHOL_REL * dmax)) {
+                        kok = i;
+                        break;
+                    }
+                    const double dd = sqrt(d);
+                    Lm[i][i] = d2(dd, 0.0);
+                    for (int r = i + 1; r < n; ++r) {
+                        double2 acc = G[r][i];
+                        for (int p = 0; p < i; ++p) acc = csub(acc, cmul(Lm[r][p], cconj(Lm[i][p])));
+                        Lm[r][i] = cscale(acc, 1.0 / dd);
+                    }
+                }
+            }
+            n = kok;
+            for (int i = 0; i < n; ++i) {
+                double2 acc = cvec[i];
+                for (int p = 0; p < i; ++p) acc = csub(acc, cmul(Lm[i][p], zz[p]));
+                zz[i] = cscale(acc, 1.0 / Lm[i][i].x);
+            }
+            for (int i = n - 1; i >= 0; --i) {
+                double2 acc = zz[i];
+                for (int p = i + 1; p < n; ++p) acc = csub(acc, cmul(cconj(Lm[p][i]), g[p]));
+                g[i] = cscale(acc, 1.0 / Lm[i][i].x);
+            }
         }
         for (int i = n; i < LMAX; ++i) g[i] = d2(0, 0);
         for (int i = 0; i < LMAX; ++i) S.gam[i] = g[i];
@@ -483,7 +629,7 @@ __device__ __forceinline__ void sc_mr_body(const ScalarArgs &a, int rhs) {
     const int lm = lmr_sh;
     for (int q = threadIdx.x; q < S.nact; q += BLOCK) {
         const int s = S.act[q];
-        ShiftState &H = a.sh[(size_t)rhs * NSMAX + s];
+        ShiftState &H = st.H[s];
         MRCoef &c = a.mc[(size_t)rhs * NSMAX + q];
         c.s = s;
         for (int k = 0; k < LMAX; ++k) c.kc[k] = d2(0, 0);
@@ -495,8 +641,10 @@ __device__ __forceinline__ void sc_mr_body(const ScalarArgs &a, int rhs) {
         const double sp = H.sp;
         double2 qs = d2(1, 0);
         double qterms = 1.0;
+        double p = 1.0;   // (-sp)^i
         for (int i = 1; i <= lm; ++i) {
-            const double2 t = cmul(g[i - 1], cpowi_neg(sp, i));
+            p *= -sp;
+            const double2 t = cmul(g[i - 1], d2(p, 0.0));
             qs = csub(qs, t);
             qterms += cmod(t);
         }
@@ -511,9 +659,14 @@ __device__ __forceinline__ void sc_mr_body(const ScalarArgs &a, int rhs) {
         }
         const double2 inv_q = cdiv(d2(1, 0), qs);
         const double2 kap = cdiv(d2(1, 0), cmul(H.zeta, H.psi));
+        // kappa sum_i g_i (-sp)^(i - 1 - k) / q, i = k + 1..lm
         for (int k = 0; k < lm; ++k) {
             double2 acc = d2(0, 0);
-            for (int i = k + 1; i <= lm; ++i) acc = cadd(acc, cmul(g[i - 1], cpowi_neg(sp, i - 1 - k)));
+            double p = 1.0;
+            for (int i = k + 1; i <= lm; ++i) {
+                acc = cadd(acc, cmul(g[i - 1], d2(p, 0.0)));
+                p *= -sp;
+            }
             c.kc[k] = cmul(kap, cmul(acc, inv_q));
         }
         c.inv_q = inv_q;
@@ -526,16 +679,18 @@ __device__ __forceinline__ void sc_mr_body(const ScalarArgs &a, int rhs) {
 // update r_0 = b - S x (FP64): when ||r_0|| has dropped below 0.1 of its
 // largest value since the last one, when any shift would freeze on the
 // recursively updated residual, or when the Krylov space looks exhausted.
-template <int NT = BLOCK>
-__device__ __forceinline__ void sc_rel_body(const ScalarArgs &a, int rhs) {
-    SeedState &S = a.seed[rhs];
-    if (!S.run || !S.mixed) return;
+template <int NT>
+__device__ __forceinline__ void sc_rel_body(const ScalarArgs &a, int rhs, StageState<NT> &st) {
+    SeedState &S = st.S;
+    if (NT == BLOCK && (!S.run || !S.mixed)) return;
     const double r02 = sum1<NT>(prow(a, rhs) + 2 * a.ps, a.nblk);
+    st.arrive();
+    if (NT != BLOCK && (!S.run || !S.mixed)) return;
     if (threadIdx.x >= 64) return;
     const double rn = sqrt(r02);
     bool due = false;
     if ((int)threadIdx.x < S.nact) {
-        const ShiftState &H = a.sh[(size_t)rhs * NSMAX + S.act[threadIdx.x]];
+        const ShiftState &H = st.H[S.act[threadIdx.x]];
         if (H.active)
             due = S.forced ? (S.m + 1 >= H.force)
                            : (rn / (cmod(cmul(H.zeta, H.psi)) * S.bnorm) <= FREEZE_FRAC * S.tol);
@@ -546,13 +701,15 @@ __device__ __forceinline__ void sc_rel_body(const ScalarArgs &a, int rhs) {
     S.rel = (rn <= 0.1 * S.rmax || freeze || S.exhausted) ? 1 : 0;
 }
 
-template <int NT = BLOCK>
-__device__ __forceinline__ void sc_conv_body(const ScalarArgs &a, int rhs) {
-    SeedState &S = a.seed[rhs];
-    if (!S.run) return;
+template <int NT>
+__device__ __forceinline__ void sc_conv_body(const ScalarArgs &a, int rhs, StageState<NT> &st) {
+    SeedState &S = st.S;
+    if (NT == BLOCK && !S.run) return;
     const double *row = prow(a, rhs);
     double re, im, r02;
     sum3<NT>(row, a.ps, a.nblk, re, im, r02);
+    st.arrive();
+    if (NT != BLOCK && !S.run) return;
     __shared__ double rn;
     if (threadIdx.x == 0) {
         rn = sqrt(r02);
@@ -573,7 +730,7 @@ __device__ __forceinline__ void sc_conv_body(const ScalarArgs &a, int rhs) {
     }
     __syncthreads();
     for (int q = threadIdx.x; q < S.nact; q += BLOCK) {
-        ShiftState &H = a.sh[(size_t)rhs * NSMAX + S.act[q]];
+        ShiftState &H = st.H[S.act[q]];
         if (!H.active) continue;
         const double res = rn / (cmod(cmul(H.zeta, H.psi)) * S.bnorm);
         H.res = res;
@@ -593,7 +750,7 @@ __device__ __forceinline__ void sc_conv_body(const ScalarArgs &a, int rhs) {
     const int s = threadIdx.x;
     bool live = false, brk = false;
     if (s < S.nshift) {
-        const ShiftState &H = a.sh[(size_t)rhs * NSMAX + s];
+        const ShiftState &H = st.H[s];
         live = H.active;
         brk = H.broken;
     }
@@ -602,7 +759,7 @@ __device__ __forceinline__ void sc_conv_body(const ScalarArgs &a, int rhs) {
     const bool anybroken = __any(brk);
     if (live) S.act[__popcll(lv & ((1ull << s) - 1ull))] = s;
     const bool ends = S.broken || S.exhausted || (S.m + 1 >= S.max_outer);
-    if (live && ends) a.sh[(size_t)rhs * NSMAX + s].iters = S.m + 1;
+    if (live && ends) st.H[s].iters = S.m + 1;
     if (threadIdx.x == 0) {
         S.nact = nact;
         S.m += 1;
@@ -636,8 +793,7 @@ __device__ __forceinline__ void sc_conv_body(const ScalarArgs &a, int rhs) {
 // with its column of each in registers.  One work-item per shift, its arrays
 // in scratch memory, took 107 us a launch at l = 4 with 16 shifts.
 template <int L>
-__device__ __forceinline__ void sc_defer_body(const ScalarArgs &a, int rhs) {
-    SeedState &S = a.seed[rhs];
+__device__ __forceinline__ void sc_defer_body(const ScalarArgs &a, int rhs, const SeedState &S) {
     if (!S.run) return;
     constexpr int nb = 2 * L + 2, self = nb;
     for (int item = threadIdx.x; item < S.nact * NDEF; item += blockDim.x) {
@@ -741,8 +897,7 @@ __device__ inline void seed_basis_replay_col(const SeedState &S, int l, int b, d
 
 // Basis form, before the MR step: every r_i and u_i of the outer iteration as
 // coefficients on its basis.
-__device__ __forceinline__ void sc_basis_body(const ScalarArgs &a, int rhs) {
-    const SeedState &S = a.seed[rhs];
+__device__ __forceinline__ void sc_basis_body(const ScalarArgs &a, int rhs, const SeedState &S) {
     if (!S.run) return;
     __shared__ double2 R[LMAX + 1][NBB], U[LMAX + 1][NBB];
     const int b = threadIdx.x;
@@ -759,12 +914,11 @@ __device__ __forceinline__ void sc_basis_body(const ScalarArgs &a, int rhs) {
 // the MR update overwrites r_0 and u_0: r_0 after the MR step at the list's
 // entries (the MR update's combined coefficients), <r~, r_0>, and the next
 // outer iteration's beta = alpha rho_1 / rho_0 with rho_0 <- -omega rho_0
-// (as its first step will find it), into seed_w[rhs] (one block per rhs).
+// (as its first step will find it), into S (one block per rhs).
 template <int L>
-__device__ __forceinline__ void basis_spec_body(const BasisArgs<double> &a, int rhs) {
-    if (!gate_open(a.gate, rhs)) return;
+__device__ __forceinline__ void basis_spec_body(const BasisArgs<double> &a, int rhs, SeedState &S) {
+    if (!S.run) return;
     constexpr int NBL = 2 * L + 2;
-    const SeedState &S = a.seed[rhs];
     __shared__ double2 c_r[NBL];
     __shared__ double2 rk[SPARSE_MAX];
     if (threadIdx.x < NBL) {
@@ -793,8 +947,8 @@ __device__ __forceinline__ void basis_spec_body(const BasisArgs<double> &a, int 
             p1 += t.x * o.y - t.y * o.x;
         }
         const double2 rho0 = cneg(cmul(S.omega, S.rho0));
-        a.seed_w[rhs].spec_rho1 = d2(p0, p1);
-        a.seed_w[rhs].beta_spec = cdiv(cmul(S.alpha, d2(p0, p1)), rho0);
+        S.spec_rho1 = d2(p0, p1);
+        S.beta_spec = cdiv(cmul(S.alpha, d2(p0, p1)), rho0);
     }
 }
 
@@ -840,19 +994,20 @@ __device__ __forceinline__ void sc_basis_replay_body(const BasisReplayArgs &a, i
 // coefficients are written for the kernel that forms it; otherwise the test
 // cannot fire and is left out.
 template <int NT>
-__device__ __forceinline__ void sc_exh_body(const ScalarArgs &a, int rhs) {
-    SeedState &S = a.seed[rhs];
+__device__ __forceinline__ void sc_exh_body(const ScalarArgs &a, int rhs, StageState<NT> &st) {
+    SeedState &S = st.S;
+    const int j = a.j;
+    const double *row = prow(a, rhs);
+    const double rj1 = sqrt(sum1<NT>(row + 4 * a.ps, a.nblk2));
+    st.arrive();
     if (!S.run || !S.bicg_on) {
         if (threadIdx.x == 0) S.exh_check = 0;
         return;
     }
-    const int j = a.j;
-    const double *row = prow(a, rhs);
-    const double rj1 = sqrt(sum1<NT>(row + 4 * a.ps, a.nblk2));
     __shared__ int check;
     __shared__ double2 R[LMAX + 1][NBB], U[LMAX + 1][NBB];
     const bool test = !S.forced && S.nact > 0;
-    const double mn = (threadIdx.x < 64 && test) ? min_shift_scale(a, S, rhs) : 0.0;
+    const double mn = (threadIdx.x < 64 && test) ? min_shift_scale(S, st.H) : 0.0;
     if (threadIdx.x == 0) {
         check = 0;
         if (test) {
