@@ -137,8 +137,8 @@ def _spinors(t: torch.Tensor, V: int, name: str) -> torch.Tensor:
     return t.contiguous()
 
 
-def _stream_handle():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream_handle() -> int:
+    return torch.cuda.current_stream().cuda_stream
 
 
 @dataclass
@@ -211,7 +211,7 @@ class Context:
         _check(lib().msb_set_store_limit(self._h, int(nbytes)))
 
     def _sync_stream(self):
-        _check(lib().msb_set_stream(self._h, _stream_handle()))
+        _check(_LIB.msb_set_stream(self._h, _stream_handle()))
 
     # -- kernel timing ------------------------------------------------------
     PROFILE_CLASSES = ("stencil", "shift_update", "shift_mr_update", "seed_vector", "scalar", "other")
@@ -244,7 +244,7 @@ class Context:
         if out is None:
             out = torch.empty_like(x)
         self._sync_stream()
-        _check(lib().wilson_apply(self._h, _P(x.data_ptr()), _P(out.data_ptr()), x.shape[0], int(flags)))
+        _check(_LIB.wilson_apply(self._h, x.data_ptr(), out.data_ptr(), x.shape[0], int(flags)))
         return out
 
     def spectral_radius(self, start: torch.Tensor, iters: int = 100) -> float:
