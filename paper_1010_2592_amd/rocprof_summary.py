@@ -191,7 +191,7 @@ def main():
     for n, c, avg, s in rows[:a.top]:
         md.append(f"| `{short(n)[:90]}` | {c} | {avg / 1e3:.2f} | {s / 1e6:.2f} | {100 * s / tot:.1f} |")
     md.append("")
-    md.append(f"Stencil launches of the solves (all `dslash` kernels, site-block and chunked, every "
+    md.append(f"Stencil launches of the solves (all `dslash` kernels, chunked and split, every "
               f"epilogue and precision, from the first solve on -- the spectral-radius estimate before "
               f"it is not part of a step; warm-up and timed steps): {len(st)} launches, average "
               f"{st_avg_us:.1f} us.  "
@@ -215,7 +215,7 @@ def main():
     os.makedirs(os.path.dirname(os.path.abspath(a.md)), exist_ok=True)
     with open(a.md, "w") as f:
         f.write("\n".join(md))
-    rec = {"kernel": "Wilson stencil (dslash_kernel and dslash_chunk_kernel, all epilogues and precisions)",
+    rec = {"kernel": "Wilson stencil (dslash_chunk_kernel and dslash_split_kernel, all epilogues and precisions)",
            "sources": STENCIL_SOURCES, "sources_sha256_16": sources_hash(),
            "workload": a.workload, "traffic_bytes_per_launch": round(traffic),
            "read_counter": read_name, "read_scale": fs, "write_scale": ws,
