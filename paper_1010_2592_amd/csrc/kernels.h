@@ -234,9 +234,8 @@ struct BasisArgs {
     const C<T> *rt = nullptr;
     // MR update with a sparse r~ (wu set): <r~, r_0> from r_0 at the list's
     // entries (into rows 0, 1), the next outer iteration's beta from it
-    // (seed_w[rhs].beta_spec) and u_0 = r_0 - beta u_0 into wu ([rhs][n])
+    // (the state's beta_spec) and u_0 = r_0 - beta u_0 into wu ([rhs][n])
     C<T> *wu = nullptr;
-    SeedState *seed_w = nullptr;
     const long *sp_idx = nullptr;     // [rhs][sp_max]
     const double2 *sp_val = nullptr;  // [rhs][sp_max]
     const int *sp_cnt = nullptr;      // [rhs], at most SPARSE_MAX

@@ -1409,7 +1409,6 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                     // iteration's beta from the basis before the MR update
                     // overwrites r_0 and u_0, then the update also makes that
                     // iteration's first direction update
-                    bm.seed_w = seed;
                     bm.sp_idx = spa.idx;
                     bm.sp_val = spa.val;
                     bm.sp_cnt = spa.cnt;
