@@ -61,6 +61,15 @@ struct StageState {
         }
         __syncthreads();
     }
+    // arrive, and whether BiCG steps go on: read by every wavefront before any
+    // may write it (a stage that breaks down clears bicg_on, and a wavefront
+    // that found it cleared would leave the others at their next barrier)
+    __device__ __forceinline__ bool arrive_bicg() {
+        arrive();
+        const bool on = S.run && S.bicg_on;
+        __syncthreads();
+        return on;
+    }
     // after the last write to it (every work-item calls it)
     __device__ __forceinline__ void leave() {
         __syncthreads();
@@ -79,6 +88,7 @@ struct StageState<BLOCK> {
     __device__ __forceinline__ StageState(const ScalarArgs &a, int rhs)
         : S(a.seed[rhs]), H(a.sh + (size_t)rhs * NSMAX) {}
     __device__ __forceinline__ void arrive() {}
+    __device__ __forceinline__ bool arrive_bicg() { return true; }   // tested before the sums, whose barriers follow
 };
 
 // sums of rows rows[0 .. cnt) of the partials, as block_sum gives each
@@ -267,8 +277,7 @@ __device__ __forceinline__ void sc_beta_body(const ScalarArgs &a, int rhs, Stage
     // fire; elsewhere it cannot (||r_0|| >= ||r_{j-1}|| / ||S||^(j-1))
     if (NT != BLOCK) {
         if (j >= 1 && !a.basis) r02 = sum1<NT>(row + 3 * a.ps, a.nblk2);
-        st.arrive();
-        if (!S.run || !S.bicg_on) return;
+        if (!st.arrive_bicg()) return;
     }
     const bool have_r0 = !a.basis || S.exh_check;
     const bool test = j >= 1 && have_r0 && !S.forced && S.nact > 0;
@@ -297,8 +306,7 @@ __device__ __forceinline__ void sc_alpha_body(const ScalarArgs &a, int rhs, Stag
     const int j = a.j;
     double re, im, u2;
     dot_sums<NT>(a, rhs, re, im, u2);
-    st.arrive();
-    if (NT != BLOCK && (!S.run || !S.bicg_on)) return;
+    if (!st.arrive_bicg()) return;
     __shared__ int ok;
     __shared__ double2 sh_alpha, sh_beta;
     if (threadIdx.x == 0) {
