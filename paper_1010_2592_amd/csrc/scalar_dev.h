@@ -22,7 +22,8 @@ constexpr int SC_THREADS = 1024;
 // The state of one right-hand side as a scalar stage works on it.  The
 // one-launch stages (NT > BLOCK) hold it in LDS: every word is loaded by a
 // work-item of its own at the start, beside the partials and before any gate
-// is known, and stored back at the end (leave) if the stage's gate was open.
+// is known, and stored back at the end (leave), unchanged where the stage's
+// gate was closed.
 // Read field by field, each dependent read (gate, list of active shifts,
 // shift) was a trip to memory of its own, since another XCD wrote it (with the
 // MR stage's factor in registers: 8^4 at l = 4, MR 15.5 us, now 13.5, alpha

@@ -1602,7 +1602,10 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
         }
     }
 
-    // ---- results of pass 1
+    // ---- results of pass 1.  The blocking copies below run on the null stream,
+    // which a non-blocking stream does not wait for, and the stages of an
+    // iteration launched ahead write the states they read back (unchanged)
+    HIPCHK(hipStreamSynchronize(st));
     std::vector<SeedState> fs(nrhs);
     std::vector<ShiftState> fsh((size_t)nrhs * NSMAX);
     HIPCHK(hipMemcpy(fs.data(), seed, nrhs * sizeof(SeedState), hipMemcpyDeviceToHost));

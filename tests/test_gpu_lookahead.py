@@ -1,0 +1,81 @@
+"""Solves launch an outer iteration ahead of the host's look at the states, but
+not where the next one begins a storage chunk of the pseudo-double pass (8
+outer iterations each), and not in the call without allocations.  Wherever the
+solve ends, what it returns is the same: forced iterations that end just
+before, at and after a chunk's end, on the default stream and on a stream that
+the null stream does not order against, the same bits."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from oracle import pfe
+from tests.helpers import A_SCALE_BOUND, cuda, host
+
+pytestmark = pytest.mark.gpu
+DIMS = (4, 4, 4, 8)
+
+
+def solve(ctx, b, m, pass_, flags, max_outer=50, ends=None):
+    """m outer iterations forced on most shifts (ends: on all of them)."""
+    sig, w = pfe.neuberger(5)
+    force = np.full(5, ends) if ends else np.array([m, max(1, m - 1), m, 1, m])
+    y, info, _ = ctx.mshift_bicgstabl(b, A_SCALE_BOUND, sig, w, 2, 1e-8, max_outer, pass_, flags=flags,
+                                      force_iters=force, allow=(0, 4, 6))
+    return host(y), info
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_1010_2592_amd import msb
+    c = msb.Context(msb.Lattice(DIMS, -2.0, 0.05, -1), cuda(wl.gauge_links(DIMS, 0.6, 3)))
+    yield c
+    c.close()
+
+
+FORMS = {"step": (1, 0), "deferred": (1, 256), "deferred basis": (1, 256 | 1024), "double": (2, 0),
+         "double basis": (2, 1024), "pseudo": (3, 0), "pseudo basis": (3, 1024), "mixed": (1, 8), "pseudo mixed": (3, 8)}
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("m", [1, 7, 8, 9, 16])
+def test_side_stream_and_chunk_ends(ctx, form, m):
+    import torch
+    b = cuda(wl.gaussian_source(DIMS, 4, 2))
+    y0, i0 = solve(ctx, b, m, *FORMS[form])
+    assert i0.outer_iters == m and np.isfinite(y0.view(np.float64)).all()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        y1, i1 = solve(ctx, b, m, *FORMS[form])
+    assert np.array_equal(y0, y1) and np.array_equal(i0.shift_iters, i1.shift_iters)
+    assert np.array_equal(i0.shift_resid, i1.shift_resid) and i0.mv_count == i1.mv_count
+    assert i0.bytes_model == i1.bytes_model
+
+
+# the iteration limit: nothing runs past it
+@pytest.mark.parametrize("form", ["step", "pseudo", "pseudo basis"])
+@pytest.mark.parametrize("limit", [1, 8, 9])
+def test_the_limit_ends_the_solve(ctx, form, limit):
+    b = cuda(wl.gaussian_source(DIMS, 4, 2))
+    y0, i0 = solve(ctx, b, 0, *FORMS[form], max_outer=limit, ends=limit + 4)
+    y1, i1 = solve(ctx, b, 0, *FORMS[form], ends=limit)
+    assert i0.status == 4 and i1.status == 0 and i0.outer_iters == i1.outer_iters == limit
+    assert np.array_equal(y0, y1) and np.array_equal(i0.shift_resid, i1.shift_resid)
+    assert np.array_equal(i0.shift_iters, i1.shift_iters)
+
+
+# a store of one chunk: the solve decides on the second one before its first
+# iteration, stores 8 and replays the rest (1e-12: the two orders of summation,
+# as in the store limit's own test)
+@pytest.mark.parametrize("m", [8, 9, 16, 17])
+def test_store_limit_at_a_chunk(ctx, m):
+    b = cuda(wl.gaussian_source(DIMS, 4, 2))
+    full, i0 = solve(ctx, b, m, 3, 0)
+    n = 12 * int(np.prod(DIMS))
+    ctx.set_store_limit(2 * 8 * 2 * 2 * n * 16)
+    try:
+        y, i1 = solve(ctx, b, m, 3, 0)
+    finally:
+        ctx.set_store_limit(0)
+    assert i0.stored_iters == m and i1.stored_iters == 8
+    assert np.linalg.norm(y - full) <= (1e-12 if m > 8 else 0.0) * np.linalg.norm(full)
