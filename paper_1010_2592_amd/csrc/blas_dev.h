@@ -418,18 +418,10 @@ __device__ __forceinline__ void basis_mr_update_body(const BasisArgs<double> &a,
         c_u[b] = vu;
     }
     __syncthreads();
+    // The vectors the completed steps wrote; the slots after them (the Mv
+    // output of a step that broke down, then what an earlier call left) have
+    // zero coefficients, and are not read: they may not be finite
     const int nbu = basis_used(S);
-    // SHIFTS: the basis vectors this outer iteration wrote, an Mv output of a
-    // step that ended after it included; the slots after them hold whatever
-    // an earlier call left
-    int nbw = 2;
-    if (SHIFTS)
-        for (int j = 0; j < L; ++j) {
-            const int f = S.step_flag[j];
-            if (f >= 1) nbw = 3 + 2 * j;
-            if (f == 2) nbw = 4 + 2 * j;
-            if (f < 2) break;
-        }
     const int nact = SHIFTS ? S.nact : 0;
     const bool first = S.m == 0;   // u^s_0 = x^s = 0: written, not read
     const DeferCoef *dc = SHIFTS ? a.dc + (size_t)rhs * NSMAX : nullptr;
@@ -450,7 +442,7 @@ __device__ __forceinline__ void basis_mr_update_body(const BasisArgs<double> &a,
         asm volatile("" ::: "memory");   // coefficients from LDS in every pass (as in the Gram kernel)
         double2 B[NBL];
 #pragma unroll
-        for (int b = 0; b < NBL; ++b) B[b] = b < (SHIFTS ? nbw : nbu) ? bvec(a, b, rhs, e) : d2(0, 0);
+        for (int b = 0; b < NBL; ++b) B[b] = b < nbu ? bvec(a, b, rhs, e) : d2(0, 0);
         double2 r0 = d2(0, 0), u0 = d2(0, 0);
 #pragma unroll
         for (int b = 0; b < NBL; ++b) {
