@@ -171,8 +171,8 @@ __device__ __forceinline__ double wave_sums(const double (&v)[N]) {
 // the number of the value whose sum wave_sums returns in this lane
 __device__ __forceinline__ int wave_sums_index() { return (int)(__brev(threadIdx.x & 63u) >> 26); }
 
-// How a wavefront's sums are formed: 1 halving the number of values at each
-// step, all VALU; 0 a shuffle tree per value, whose registers are fewer (the
+// How a wavefront's sums are formed: 1 all VALU, halving the number of many
+// values at each step; 0 a shuffle tree per value, whose registers are fewer (the
 // persistent kernel sets 0 before including this header: its register budget
 // is the maximum over all its stages, and the other form took its FP64
 // instances from two wavefronts per SIMD to one).  The sums are the same bits.
@@ -181,13 +181,25 @@ __device__ __forceinline__ int wave_sums_index() { return (int)(__brev(threadIdx
 #endif
 
 // Reduce NV <= 64 doubles over the 64 lanes of a wavefront (the same data
-// always gives the same bits) and store value k at out[k * stride].
+// always gives the same bits) and store value k at out[k * stride].  Up to
+// three values are summed one after another: halved together they are all live
+// to the end, which in the chunked FP64 stencil with r~ (255 VGPRs) took two
+// AGPRs and with them the second wavefront per SIMD (12 dense sources, 12^3x24:
+// 114 us, now 99; 16^3x32: 324, now 300; 4 sources there: 122, now 103).
 template <int NV>
 __device__ inline void wave_reduce_store(const double (&v)[NV], double *out, long stride) {
 #if MSB_WAVE_SUMS
-    const double x = wave_sums<NV>(v);
-    const int k = wave_sums_index();
-    if (k < NV) out[(size_t)k * stride] = x;
+    if constexpr (NV <= 3) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const double x = wave_sum(v[k]);
+            if ((threadIdx.x & 63) == 0) out[(size_t)k * stride] = x;
+        }
+    } else {
+        const double x = wave_sums<NV>(v);
+        const int k = wave_sums_index();
+        if (k < NV) out[(size_t)k * stride] = x;
+    }
 #else
     const int lane = threadIdx.x & 63;
 #pragma unroll
