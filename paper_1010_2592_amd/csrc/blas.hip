@@ -38,8 +38,20 @@ __global__ __launch_bounds__(BLOCK) void k_seed_u(VecArgs<T> a) {
     seed_u_body<T, J, ONE>(a, blockIdx.x, gridDim.x, blockIdx.y);
 }
 
+// Wavefronts per SIMD the compiler has to leave room for (1: its own choice).
+// Left to itself it takes a few registers too many in these since the fused
+// r-update completes ended steps and the sums over a wavefront are VALU
+// (FP32, 16^3x32): the per-step single pass's j = 1 update, 66 registers,
+// 212 us (202 with 57), and the double pass's MR update at l = 7 and 8, 2
+// right-hand sides, 87 and 95 registers, 125 and 138 us (119 and 130).  The
+// j = 3 update is faster with its 85 registers (301 us) than with 73 (363).
 template <typename T, int J, bool SHIFTS, bool XH, bool FU>
-__global__ __launch_bounds__(BLOCK) void k_r_update(VecArgs<T> a) {
+constexpr int r_update_waves() { return sizeof(T) == 4 && J == 1 && SHIFTS && XH && FU ? 8 : 1; }
+template <typename T, int L, bool SHIFTS, bool XH>
+constexpr int mr_update_waves() { return sizeof(T) == 4 && L >= 7 && !SHIFTS && XH ? 6 : 1; }
+
+template <typename T, int J, bool SHIFTS, bool XH, bool FU>
+__global__ __launch_bounds__(BLOCK, (r_update_waves<T, J, SHIFTS, XH, FU>())) void k_r_update(VecArgs<T> a) {
     r_update_body<T, J, SHIFTS, XH, FU>(a, blockIdx.x, gridDim.x, blockIdx.y);
 }
 
@@ -47,7 +59,7 @@ template <typename T, int L>
 __global__ __launch_bounds__(BLOCK) void k_gram(VecArgs<T> a) { gram_body<T, L>(a, blockIdx.x, gridDim.x, blockIdx.y); }
 
 template <typename T, int L, bool SHIFTS, bool XH>
-__global__ __launch_bounds__(BLOCK) void k_mr_update(VecArgs<T> a) {
+__global__ __launch_bounds__(BLOCK, (mr_update_waves<T, L, SHIFTS, XH>())) void k_mr_update(VecArgs<T> a) {
     mr_update_body<T, L, SHIFTS, XH>(a, blockIdx.x, gridDim.x, blockIdx.y);
 }
 
