@@ -193,10 +193,10 @@ bool stencil_timing_taken() {
 template <typename T, int EPI, bool G5IN>
 static void launch_form(hipStream_t st, DslashArgs<T> a, int nrhs) {
     const int nch = (a.g.V + CHUNK - 1) / CHUNK;
-    if (dslash_use_split(nch, nrhs))
+    if (dslash_use_split<T, EPI, G5IN>(nch, nrhs))
         dispatch<T>(dslash_split_kernel<T, EPI, G5IN>, dim3((unsigned)dslash_split_prepare(a, nrhs)), dim3(256), st, a);
     else
-        dispatch<T>(dslash_chunk_kernel<T, EPI, G5IN>, dim3((unsigned)dslash_chunk_prepare(a, nrhs)),
+        dispatch<T>(dslash_chunk_kernel<T, EPI, G5IN>, dim3((unsigned)dslash_chunk_prepare<T, G5IN>(a, nrhs)),
                     dim3(64 * CHUNK_WAVES), st, a);
 }
 

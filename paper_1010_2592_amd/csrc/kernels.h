@@ -77,9 +77,6 @@ inline long dslash_prepare(DslashArgs<T> &a, int nrhs) {
 
 constexpr int CHUNK = 64;
 constexpr int CHUNK_WAVES = 4;   // wavefronts per block of the chunked stencil
-// Blocks of the chunked stencil the chip holds at a time: two per CU by the
-// 74 KB of links an FP64 block stages and by its registers, 256 CUs.
-constexpr int CHUNK_RESIDENT = 512;
 // Slabs of chunks per XCD (see slab_chunk).
 template <typename T>
 inline void dslash_slab_prepare(DslashArgs<T> &a, int nrhs) {
@@ -91,15 +88,30 @@ inline void dslash_slab_prepare(DslashArgs<T> &a, int nrhs) {
     a.per_t = a.tsc ? ((a.per + a.tsc - 1) / a.tsc) * a.tsc : a.per;
 }
 // Which form: the split stencil (a block per chunk and right-hand side) for
-// one right-hand side, which has no links to share, and while the chip would
-// hold its blocks in two rounds: 8 vectors on 8^4 (512 blocks) take 7.3 us
-// against 9.5 in the chunked form, 6 on 10x9x7x14 (828) 11.6 against 12.4, 16
-// on 8^4 (1024) 12.9 against 10.7 (plain epilogue, FP64).  With 2 or 3
-// right-hand sides the chunked form leaves wavefronts idle and the line lies
-// at three rounds: 2 on 12^3x24 (1296) 22.0 against 24.3 us, 3 (1944) 21.9
-// against 20.9, 2 on 16^3x32 (4096) 49 against 42.
-inline bool dslash_use_split(long nch, int nrhs) {
-    return nrhs == 1 || nch * nrhs < (nrhs < CHUNK_WAVES ? 3 : 2) * (long)CHUNK_RESIDENT;
+// one right-hand side, which has no links to share, and below a number of
+// blocks that depends on the epilogue; the chunked form beyond.  The more
+// operands the epilogue reads beside the hops, the longer the split form's
+// wider loads pay; with 2 or 3 right-hand sides the chunked form leaves
+// wavefronts idle.  Launch times, split / chunked in us (FP64; FP32 has the
+// same lines), on either side of each line:
+//   at most v and w        2, 3 sources: 1944 blocks (12^3x24, EPI_SV) 24.8 / 27.0,
+//                          2304 (16^3x12) 32.3 / 31.8, 3072 (16^3x24, plain) 41.1 / 34.6
+//                          4 and more: 828 (10x9x7x14) 14.7 / 17.2, 1024 (8^3x32) 14.5 / 13.6
+//   r~ (EPI_MV)            2, 3: 3072 (16^3x24) 44.6 / 46.5, 4096 (16^3x32) 68.2 / 61.9
+//                          4 and more: 1944 (12^4) 31.8 / 36.4, 3072 (8^3x32) 41.5 / 39.0
+//   y (EPI_MV_Y)           4096 (16^3x32, 2) 75.0 / 81.5, 3888 (12^4, 12) 60.5 / 77.2,
+//                          4096 (16^4, 4) 63.2 / 61.0, 4608 (16^3x24, 3) 76.8 / 74.7
+//   gamma5 on the input,   2, 3: 4608 (16^3x24) 47.0 / 52.3, 6144 (16^3x32) 78.8 / 71.0
+//   FP64 (one wavefront    4 and more: 1024 (8^4) 14.2 / 11.6
+//   per SIMD if chunked)
+template <typename T, int EPI, bool G5IN>
+constexpr bool dslash_use_split(long nch, int nrhs) {
+    const bool few = nrhs < CHUNK_WAVES;
+    long blocks = few ? 2048 : 1024;
+    if (EPI == EPI_MV) blocks = few ? 3200 : 2048;
+    if (EPI == EPI_MV_Y) blocks = 4200;
+    if (G5IN && sizeof(T) == 8) blocks = few ? 4700 : 1024;
+    return nrhs == 1 || nch * nrhs < blocks;
 }
 // Launch geometry of the split stencil; returns its number of blocks.
 template <typename T>
@@ -109,21 +121,22 @@ inline long dslash_split_prepare(DslashArgs<T> &a, int nrhs) {
 }
 // Launch geometry of the chunked stencil; returns its number of blocks.
 //
-// One block per chunk sweeps every right-hand side while the chunks fill the
-// chip's resident blocks four times over or more.  Below that the last,
-// partly filled round of blocks costs too much, and each block takes at most
-// one right-hand side per wavefront instead (balanced groups), staging its
-// links again from the caches: 12 sources on 12^3x24 (648 chunks, 1.3
-// rounds) took 94 / 80 us per Mv (with / without r~) in one group and take
-// 88 / 76 in three; on 8^4 (64 chunks) 16 vectors took 19 us, now 11 (plain
-// epilogue).  With 2048 chunks (16^3x32, 12 sources) one group stays ahead,
-// 244 us against 250, and with 6 sources, 118 against 124.
-template <typename T>
+// One block per chunk sweeps every right-hand side while the chunks alone fill
+// the chip (512 FP64 blocks at a time, by the 74 KB of links each stages and
+// its registers).  Below 768 chunks each block takes at most one right-hand
+// side per wavefront instead (balanced groups), staging its links again from
+// the caches: EPI_MV, one group / groups, 12 sources on 8^4 (64 chunks) 30.0 /
+// 15.7 us, on 12^3x24 (648) 103.9 / 98.3, 24 there 197.7 / 182.0; 12 on
+// 16^3x12 (768) 119.2 / 120.4, on 16^4 (1024) 134.7 / 143.0.  With gamma5 on
+// the input in FP64, one wavefront per SIMD, staging again costs more and the
+// line lies at 256 chunks: 12 on 10x9x7x14 (138) 23.5 / 20.5, on 8^3x32 (256)
+// 25.8 / 28.0, on 16^4 103.9 / 119.1.
+template <typename T, bool G5IN>
 inline long dslash_chunk_prepare(DslashArgs<T> &a, int nrhs) {
     dslash_slab_prepare(a, nrhs);
     a.sstride = 1 << 30;
     int groups = 1;
-    if (a.nch < 4 * CHUNK_RESIDENT) groups = (nrhs + CHUNK_WAVES - 1) / CHUNK_WAVES;
+    if (a.nch < (G5IN && sizeof(T) == 8 ? 256 : 768)) groups = (nrhs + CHUNK_WAVES - 1) / CHUNK_WAVES;
     a.rpb = (nrhs + groups - 1) / groups;
     groups = (nrhs + a.rpb - 1) / a.rpb;
     return 8L * a.per_t * groups;
