@@ -19,7 +19,7 @@
 //
 // Every inner-iteration decision is taken on the device (scalar kernels); the
 // host waits once per outer iteration to learn whether any right-hand side is
-// still running, with the next iteration already launched.
+// still running, on small problems with the next iteration already launched.
 #include <algorithm>
 #include <cmath>
 #include <complex>
@@ -1539,17 +1539,28 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
         CHK(run_persistent<T>(c, persist_ops1, max_outer, true, l, seed, nrhs, nullptr));
     } else {
         // The host learns after each outer iteration whether any right-hand
-        // side still runs.  It launches the next iteration before it waits
-        // for that, so the stream does not idle over the copy, the wake-up
-        // and the first launches (10 to 15 us an iteration); where nothing
-        // ran any more, the gates of the iteration launched too many are all
-        // closed.  Not where the next iteration begins with a decision on the
-        // store's memory, and not with timed launches (whose records carry
-        // the byte counts of the right-hand sides that run) or pageable
-        // staging (a call without allocations).
+        // side still runs.  On small problems it launches the next iteration
+        // before it waits for that, so the stream does not idle over the copy,
+        // the wake-up and the first launches; where nothing ran any more, the
+        // gates of the iteration launched too many are all closed.  What that
+        // saves per iteration and what a closed one costs (l = 4, FP64, single
+        // pass deferred / double pass):
+        //   one source on 4^3x8      37 / 15 us against 60,
+        //   on 8^4                   29 / 5 against 70,
+        //   6 sources on 8^4         14 / 1 against 90,
+        //   one source on 12^3x24    10 / 8 against 110,
+        //   on 16^3x32               10 / 8 against 150,
+        //   4 sources on 12^3x24     2 / -8 against 160,
+        //   12 sources on 16^3x32    15 / -10 against 280.
+        // So not beyond 65536 sites of all right-hand sides, and not where
+        // this iteration is likely the last.  Nor where the next iteration
+        // begins with a decision on the store's memory, with timed launches
+        // (whose records carry the byte counts of the right-hand sides that
+        // run) or with pageable staging (a call without allocations).
+        constexpr long AHEAD_SITES = 65536;
         int nr_run = nrhs;                       // right-hand sides that run iteration m
         double nsh_act = (double)nrhs * ns;      // active shifts over those
-        const bool ahead = !c->prof && !c->arena;
+        const bool ahead = !c->prof && !c->arena && (long)nrhs * V <= AHEAD_SITES;
         if (ahead)
             for (hipEvent_t &ev : c->look)
                 if (!ev) HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
@@ -1572,11 +1583,25 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
             if (ahead) HIPCHK(hipEventRecord(c->look[m & 1], st));
             return 0;
         };
+        // ||r_0|| after the last two iterations the host has seen, and where
+        // the last one leaves every right-hand side done: the smallest shift,
+        // which is the seed's own, converges with it
+        std::vector<double> rn(nrhs), rn_prev(nrhs), rn_end(nrhs, -1.0);
+        const int force_max =
+            P.force_iters ? *std::max_element(P.force_iters, P.force_iters + (size_t)nrhs * ns) : max_outer;
+        auto likely_last = [&](int m) {
+            if (m + 1 >= force_max) return true;
+            if (P.force_iters || m == 0) return false;
+            for (int r = 0; r < nrhs; ++r)
+                // the last reduction once more, within a factor 2 of the end
+                if (rn[r] * std::min(1.0, rn[r] / rn_prev[r]) > 2.0 * rn_end[r] && rn_end[r] >= 0.0) return false;
+            return true;
+        };
         CHK(launch_outer(0, nr_run, nsh_act));
         for (int m = 0;; ++m) {
             const bool more = m + 1 < max_outer;
             bool launched = false;
-            if (ahead && more && !(pass3 && m + 1 < m_split && (m + 1) % PSC == 0)) {
+            if (ahead && more && !likely_last(m) && !(pass3 && m + 1 < m_split && (m + 1) % PSC == 0)) {
                 const double bytes = c->bytes_acc;
                 CHK(launch_outer(m + 1, 0, 0));
                 c->bytes_acc = bytes;            // counted below, once it is known what runs it
@@ -1591,6 +1616,9 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                     nr_run += 1;
                     nsh_act += S.nact;
                 }
+                rn_prev[r] = m == 0 ? S.bnorm : rn[r];
+                rn[r] = S.rnorm0;
+                rn_end[r] = S.run ? FREEZE_FRAC * S.tol * S.bnorm : -1.0;
             }
             if (nr_run == 0 || !more) break;
             if (launched) {
