@@ -113,20 +113,13 @@ __global__ __launch_bounds__(BLOCK) void k_defer_update(VecArgs<T> a) {
         a.W0[((size_t)rhs * a.nshift + d.s) * n + e] = un;
         a.X[((size_t)rhs * a.nshift + d.s) * n + e] = xn;
     };
-    // basis vectors this outer iteration wrote (r_0, u_0, then the Mv outputs
-    // of the steps it made): the slots after them hold whatever an earlier
-    // call left, which zero coefficients must not meet (0 * NaN)
-    int nbw = 2;
-    for (int j = 0; j < L; ++j) {
-        const int f = a.seed[rhs].step_flag[j];
-        if (f >= 1) nbw = 3 + 2 * j;
-        if (f == 2) nbw = 4 + 2 * j;
-        if (f < 2) break;
-    }
+    // the vectors the completed steps wrote (see basis_mr_update_body): the
+    // slots after them have zero coefficients and may not be finite
+    const int nbu = basis_used(a.seed[rhs]);
     for (long e = (long)blockIdx.x * BLOCK + threadIdx.x; e < n; e += (long)gridDim.x * BLOCK) {
         C<T> b[NB];
 #pragma unroll
-        for (int k = 0; k < NB; ++k) b[k] = k < nbw ? B[k * n + e] : mk<T>(0, 0);
+        for (int k = 0; k < NB; ++k) b[k] = k < nbu ? B[k * n + e] : mk<T>(0, 0);
         // two shifts at a time: their four loads issue together (every
         // shift's vectors exist; a shift that stopped is loaded, not written)
         int q = 0;
