@@ -209,8 +209,8 @@ void launch_dslash(hipStream_t st, DslashArgs<T> a, int nrhs, int epi, bool g5in
     else if (epi == EPI_SV) launch_form<T, EPI_SV, false>(st, a, nrhs);
     else if (epi == EPI_SV2) launch_form<T, EPI_SV2, false>(st, a, nrhs);
     else if (epi == EPI_MVN) launch_form<T, EPI_MVN, false>(st, a, nrhs);
-    else if (epi == EPI_MVV) launch_form<T, EPI_MVV, false>(st, a, nrhs);
-    else launch_form<T, EPI_MV_Y, false>(st, a, nrhs);
+    else if (epi == EPI_MV_Y) launch_form<T, EPI_MV_Y, false>(st, a, nrhs);
+    else if constexpr (sizeof(T) == 8) launch_form<T, EPI_MVV, false>(st, a, nrhs);   // CG is FP64
 }
 
 template void launch_dslash<double>(hipStream_t, DslashArgs<double>, int, int, bool);

@@ -857,7 +857,10 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
     // when it starts)
     const bool mixed = sizeof(T) != sizeof(double);
     const bool deferred = pass1 && P.deferred;
-    const int nb = 2 * l + 2;                  // deferred: basis vectors per outer iteration
+    const bool basis = P.seed_basis && !mixed && !P.persistent && (!pass1 || deferred);
+    // deferred: basis vectors kept per outer iteration (in the seed's basis
+    // form without r_0 and u_0, which stay in place)
+    const int nb = 2 * l + (basis ? 0 : 2);
     const int wslots = deferred ? 1 : l + 1;   // shift vectors kept per shift
     constexpr int SPMAX = SPARSE_MAX;          // sparse shadow residual: entries per rhs
     constexpr int NBL = 256;                   // blocks of its scan
@@ -911,7 +914,6 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
     }
     // basis form of the seed: the two vectors each BiCG step feeds its Mv
     // (u_j, r_j after their updates) and the basis coefficients
-    const bool basis = P.seed_basis && !mixed && !P.persistent && (!pass1 || deferred);
     if (basis) {
         CHK(ensure(c, c->ws_bw, (size_t)2 * nrhs * n * cs));
         CHK(ensure(c, c->ws_sb, (size_t)nrhs * sizeof(SeedBasis)));
@@ -1269,7 +1271,7 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
         }
         // Mv output t of this outer iteration (t = 2j: u_{j+1}, 2j + 1:
         // r_{j+1}): its slot in the pass-3 store, or in the deferred single
-        // pass's basis (after B_0 = r_0, B_1 = u_0)
+        // pass's basis (after B_0 = r_0, B_1 = u_0 where it keeps them)
         const bool keep = pass3 && m < m_split;   // pass 3: this iteration's outputs are stored
         const bool stored = keep || deferred;
         const long store_rs = pass3 ? ps_rs : (long)nb * n;
