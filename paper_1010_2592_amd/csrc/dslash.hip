@@ -46,7 +46,8 @@ __global__ __launch_bounds__(256) void dslash_split_kernel(DslashArgs<T> a) {
 }
 
 // 4 wavefronts per block of the chunked stencil (FP64: two blocks per CU by
-// the 74 KB of staged links and by registers; FP32: three, 96 chunks resident
+// the 74 KB of staged links and by registers, one with gamma5 on the input,
+// which takes 270 registers; FP32: three, 96 chunks resident
 // per XCD, whose z-t checkerboard reads overlap in L2 better than those of
 // one 12-wavefront block per CU)
 template <typename T, int EPI, bool G5IN>

@@ -38,9 +38,11 @@ import re
 import sqlite3
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-# the stencil kernels, and the solver that chooses which of their epilogues
-# run: a change to either lapses the measured traffic
+# the stencil kernels with the headers they are built from (the launch rules
+# and geometry, the sums), and the solver that chooses which of their
+# epilogues run: a change to any of them lapses the measured traffic
 STENCIL_SOURCES = ["paper_1010_2592_amd/csrc/stencil_dev.h", "paper_1010_2592_amd/csrc/dslash.hip",
+                   "paper_1010_2592_amd/csrc/kernels.h", "paper_1010_2592_amd/csrc/common.h",
                    "paper_1010_2592_amd/csrc/solver.hip"]
 COPY_KIB = 1048576.0
 
