@@ -858,9 +858,10 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
     const bool mixed = sizeof(T) != sizeof(double);
     const bool deferred = pass1 && P.deferred;
     const bool basis = P.seed_basis && !mixed && !P.persistent && (!pass1 || deferred);
-    // deferred: basis vectors kept per outer iteration (in the seed's basis
-    // form without r_0 and u_0, which stay in place)
-    const int nb = 2 * l + (basis ? 0 : 2);
+    // deferred: basis vectors per outer iteration.  In the seed's basis form
+    // r_0 and u_0 stay in place and the first two rows are only room between
+    // the right-hand sides' rows
+    const int nb = 2 * l + 2;
     const int wslots = deferred ? 1 : l + 1;   // shift vectors kept per shift
     constexpr int SPMAX = SPARSE_MAX;          // sparse shadow residual: entries per rhs
     constexpr int NBL = 256;                   // blocks of its scan
@@ -1271,13 +1272,13 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
         }
         // Mv output t of this outer iteration (t = 2j: u_{j+1}, 2j + 1:
         // r_{j+1}): its slot in the pass-3 store, or in the deferred single
-        // pass's basis (after B_0 = r_0, B_1 = u_0 where it keeps them)
+        // pass's basis (after B_0 = r_0, B_1 = u_0)
         const bool keep = pass3 && m < m_split;   // pass 3: this iteration's outputs are stored
         const bool stored = keep || deferred;
         const long store_rs = pass3 ? ps_rs : (long)nb * n;
         auto slot = [&](int t) {
             return pass3 ? (C<T> *)c->pstore[m / PSC].p + ((size_t)(m % PSC) * 2 * l + t) * n
-                         : Bm + (size_t)(nb - 2 * l + t) * n;
+                         : Bm + (size_t)(2 + t) * n;
         };
         auto from_store = [&](VecArgs<T> &x, int ri, int ui) {
             x.r_src_i = (stored && ri >= 1) ? ri : -1;
