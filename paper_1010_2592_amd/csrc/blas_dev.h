@@ -420,8 +420,12 @@ __device__ __forceinline__ void basis_mr_update_body(const BasisArgs<double> &a,
     __syncthreads();
     // The vectors the completed steps wrote; the slots after them (the Mv
     // output of a step that broke down, then what an earlier call left) have
-    // zero coefficients, and are not read: they may not be finite
-    const int nbu = basis_used(S);
+    // zero coefficients, and are not read: they may not be finite.  With the
+    // shifts the compiler is not told that the number is even: it then loads
+    // in pairs of vectors, 3100 us instead of 2935 (12 sources, 16^3x32, l = 4,
+    // 8 shifts)
+    int nbu = basis_used(S);
+    if (SHIFTS) asm("" : "+s"(nbu));
     const int nact = SHIFTS ? S.nact : 0;
     const bool first = S.m == 0;   // u^s_0 = x^s = 0: written, not read
     const DeferCoef *dc = SHIFTS ? a.dc + (size_t)rhs * NSMAX : nullptr;
