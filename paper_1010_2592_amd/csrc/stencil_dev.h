@@ -559,8 +559,14 @@ __device__ __forceinline__ void dslash_chunk(const DslashArgs<T> &a, int p) {
         double part[3] = {0.0, 0.0, 0.0};
         dslash_sites<T, EPI, G5IN>(a, lk, o.in, o.out, o.v, o.rt, o.y, o.yc, o.sig0, o.w, base + lane, part);
         double *prow = a.part + (size_t)rhs * PMAX * a.ps + chunk;
-        if (EPI == EPI_MVV) wave_reduce_store<1>({part[0]}, prow, a.ps);
-        else if (epi_dots(EPI)) wave_reduce_store<3>(part, prow, a.ps);
+        if (EPI == EPI_MVV) {
+            wave_reduce_store<1>({part[0]}, prow, a.ps);
+        } else if (EPI == EPI_MVN) {
+            wave_reduce_store<1>({part[2]}, prow + 2 * a.ps, a.ps);
+            if (lane == 0) prow[0] = prow[a.ps] = 0.0;
+        } else if (epi_dots(EPI)) {
+            wave_reduce_store<3>(part, prow, a.ps);
+        }
     }
 }
 
