@@ -19,7 +19,8 @@
 //
 // Every inner-iteration decision is taken on the device (scalar kernels); the
 // host waits once per outer iteration to learn whether any right-hand side is
-// still running, on small problems with the next iteration already launched.
+// still running, with the next iteration already launched unless this one is
+// likely the last.
 #include <algorithm>
 #include <cmath>
 #include <complex>
@@ -1542,28 +1543,23 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
         CHK(run_persistent<T>(c, persist_ops1, max_outer, true, l, seed, nrhs, nullptr));
     } else {
         // The host learns after each outer iteration whether any right-hand
-        // side still runs.  On small problems it launches the next iteration
-        // before it waits for that, so the stream does not idle over the copy,
-        // the wake-up and the first launches; where nothing ran any more, the
-        // gates of the iteration launched too many are all closed.  What that
-        // saves per iteration and what a closed one costs (l = 4, FP64, single
-        // pass deferred / double pass):
-        //   one source on 4^3x8      37 / 15 us against 60,
-        //   on 8^4                   29 / 5 against 70,
-        //   6 sources on 8^4         14 / 1 against 90,
-        //   one source on 12^3x24    10 / 8 against 110,
-        //   on 16^3x32               10 / 8 against 150,
-        //   4 sources on 12^3x24     2 / -8 against 160,
-        //   12 sources on 16^3x32    15 / -10 against 280.
-        // So not beyond 65536 sites of all right-hand sides, and not where
-        // this iteration is likely the last.  Nor where the next iteration
-        // begins with a decision on the store's memory, with timed launches
-        // (whose records carry the byte counts of the right-hand sides that
-        // run) or with pageable staging (a call without allocations).
-        constexpr long AHEAD_SITES = 65536;
+        // side still runs.  It launches the next iteration before it waits
+        // for that, so the stream does not idle over the copy, the wake-up
+        // and the first launches: 15 to 50 us an iteration, from one source on
+        // 4^3x8 to 12 on 16^3x32 and from one host to another (sign(H) b on
+        // 4^3x8 5.7 ms, 5.1 with it; f(A) b of 12 sources on 12^3x24 112.9 and
+        // 112.5; on 16^3x32 343.9 and 340.3 on a slow host, 352.4 and 352.1 on
+        // another).  Where nothing ran any more, the gates of the iteration
+        // launched too many are all closed, which takes 60 us for one source
+        // on 4^3x8 and 280 for 12 on 16^3x32, more than it saves there in a
+        // short solve.  So it waits where this iteration is likely the last.
+        // Also where the next iteration begins with a decision on the store's
+        // memory, with timed launches (whose records carry the byte counts of
+        // the right-hand sides that run) and with pageable staging (a call
+        // without allocations).
         int nr_run = nrhs;                       // right-hand sides that run iteration m
         double nsh_act = (double)nrhs * ns;      // active shifts over those
-        const bool ahead = !c->prof && !c->arena && (long)nrhs * V <= AHEAD_SITES;
+        const bool ahead = !c->prof && !c->arena;
         if (ahead)
             for (hipEvent_t &ev : c->look)
                 if (!ev) HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
@@ -1586,18 +1582,21 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
             if (ahead) HIPCHK(hipEventRecord(c->look[m & 1], st));
             return 0;
         };
-        // ||r_0|| after the last two iterations the host has seen, and where
-        // the last one leaves every right-hand side done: the smallest shift,
-        // which is the seed's own, converges with it
-        std::vector<double> rn(nrhs), rn_prev(nrhs), rn_end(nrhs, -1.0);
+        // ||r_0|| relative to ||b|| after the last iteration the host has seen
+        // and where it leaves a right-hand side done (the smallest shift, which
+        // is the seed's own, converges with it; done already: -1)
+        std::vector<double> rn(nrhs), rn_end(nrhs, -1.0);
         const int force_max =
             P.force_iters ? *std::max_element(P.force_iters, P.force_iters + (size_t)nrhs * ns) : max_outer;
         auto likely_last = [&](int m) {
             if (m + 1 >= force_max) return true;
-            if (P.force_iters || m == 0) return false;
+            if (P.force_iters) return false;
+            // nothing seen yet: a solve of one iteration is more likely a
+            // loss on a large problem
+            if (m == 0) return (long)nrhs * V > 65536;
             for (int r = 0; r < nrhs; ++r)
-                // the last reduction once more, within a factor 2 of the end
-                if (rn[r] * std::min(1.0, rn[r] / rn_prev[r]) > 2.0 * rn_end[r] && rn_end[r] >= 0.0) return false;
+                // one more mean reduction leaves it a factor 2 from its end or more
+                if (rn_end[r] >= 0.0 && rn[r] * std::min(1.0, std::pow(rn[r], 1.0 / m)) > 2.0 * rn_end[r]) return false;
             return true;
         };
         CHK(launch_outer(0, nr_run, nsh_act));
@@ -1619,9 +1618,8 @@ static int solve_impl(Ctx *c, const SolveParams &P, const double2 *b, double2 *y
                     nr_run += 1;
                     nsh_act += S.nact;
                 }
-                rn_prev[r] = m == 0 ? S.bnorm : rn[r];
-                rn[r] = S.rnorm0;
-                rn_end[r] = S.run ? FREEZE_FRAC * S.tol * S.bnorm : -1.0;
+                rn[r] = S.rnorm0 / S.bnorm;
+                rn_end[r] = S.run ? FREEZE_FRAC * S.tol : -1.0;
             }
             if (nr_run == 0 || !more) break;
             if (launched) {

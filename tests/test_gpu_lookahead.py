@@ -1,6 +1,7 @@
 """Solves launch an outer iteration ahead of the host's look at the states, but
-not where the next one begins a storage chunk of the pseudo-double pass (8
-outer iterations each), and not in the call without allocations.  Wherever the
+not past one that is likely the last, not where the next one begins a storage
+chunk of the pseudo-double pass (8 outer iterations each), and not in the call
+without allocations.  Wherever the
 solve ends, what it returns is the same: forced iterations that end just
 before, at and after a chunk's end, on the default stream and on a stream that
 the null stream does not order against, the same bits."""
@@ -52,8 +53,8 @@ def test_side_stream_and_chunk_ends(ctx, form, m):
     assert i0.bytes_model == i1.bytes_model
 
 
-# solves that end by themselves, mostly where the host did not expect it: on
-# 12^3x24 with 2 sources (82944 sites) nothing is launched ahead
+# solves that end by themselves, where the host expects it and where not; with
+# 2 sources on 12^3x24 (82944 sites) it waits for the first iteration
 @pytest.mark.parametrize("dims,nrhs", [(DIMS, 1), ((8, 8, 8, 8), 3), ((12, 12, 12, 24), 1), ((12, 12, 12, 24), 2)])
 @pytest.mark.parametrize("form", ["step", "deferred basis", "double", "pseudo basis"])
 @pytest.mark.parametrize("tol", [0.3, 1e-3, 1e-6])
